@@ -13,24 +13,41 @@
 //     scan).  Every chunk has the same number of edges, however skewed the
 //     degrees: a hub's edges spread over many chunks.
 //   * Per chunk, the workgroup loads the frontier vertices its ranks fall in
-//     (a table written while the frontier was built gives the first one),
-//     maps each rank to its vertex by a search in LDS, and claims every
-//     endpoint not yet discovered by setting its bit in the visited bitmap
-//     with an atomic or: the lane that flips the bit wins.  The winners are the
-//     vertices of the next level that this chunk discovered; those with
-//     edges are kept in LDS with their degrees (a chunk discovers at most
-//     one vertex per edge, so they always fit).
-//   * Where they go in the next frontier is a scan over chunks: the chunk
-//     publishes (vertices, edges) packed in one 64-bit value in its flag
-//     words at once, obtains its offsets from its own previous chunk's
-//     running total and the values of the chunks in between (the window
-//     fold of the scan), and writes its vertices, their edge offsets and
-//     the next level's chunk table there.  No shared tail counter.
-//   * A level ends with a grid barrier built from the same flag words: each
-//     workgroup publishes its sums under the level's tag, workgroup 0 adds
-//     them up and publishes the totals, which every workgroup waits for.
-//     The next frontier's writes are released before the arrival and
-//     acquired after the release word, at agent scope.
+//     (a table written while the frontier was built gives the first one) and
+//     maps each rank to its vertex by counting heads in LDS (map_ranks).
+//   * What is found goes one of three ways, by the level's edges D:
+//     - D >= kBfsWideEdges and D >= V / 4 (wide_level): endpoints are marked
+//       with plain byte stores and the next frontier is gathered by a sweep
+//       over the marks, the workgroups' counts handed forward through flag
+//       words.  Bound by random reads of the marks: on an R-MAT graph of 2^22
+//       vertices and 2^27 column entries the largest level (109 M edges) takes
+//       450 us, 240 G edges/s, against 65 G edges/s for the chunks below (a
+//       probe reads random words of a 4 MiB array at 250 G/s and makes 27 G
+//       atomics/s at any scope).  Neither bits set by atomics (1040 us: every
+//       atomic takes the line from eight L2s) nor one map of marks per XCD
+//       (456 us, and eight times the sweep) did better.
+//     - D <= kBfsChunkEdges (solo_levels): workgroup 0 runs the level alone,
+//       and the small ones after it, with the frontier in LDS: 2.3 us a level
+//       on a path of single vertices, against 6.9 us with chunks and a grid
+//       barrier per level.
+//     - otherwise, chunk by chunk: every endpoint not yet found is claimed by
+//       an atomic or on its mark; the chunk's winners are staged in LDS (one
+//       discovery per edge at most, so they always fit), it publishes
+//       (vertices, edges) packed in one 64-bit value in its flag words at
+//       once, obtains its offsets from its own previous chunk's running total
+//       and the values of the chunks in between (the window fold of the
+//       scan), and writes its vertices, their edge offsets and the next
+//       level's chunk table there.  No shared tail counter.  Up to 2^20 edges
+//       this is as fast as a sweep and its extra barrier (R-MAT 2^18, 0.9 M
+//       edges: 16-24 us).
+//   * A level (or run of solo levels) ends with a grid barrier built from the
+//     same flag words: each workgroup publishes its sums under the level's
+//     tag, workgroup 0 adds them up and publishes the totals, which every
+//     workgroup waits for.  The next frontier's writes are released before
+//     the arrival and acquired after the release word, at agent scope.  One
+//     workgroup of 1024 threads per CU: a barrier, a window and a sweep then
+//     have 256 members (four of 256 threads: R-MAT 2^18 379 us a search,
+//     2^20 653, against 191 and 357).
 //   * Every flag word carries the tag of its level, so nothing is cleared
 //     between levels or launches; the host hands each launch a fresh range
 //     of tags.  Every wait is bounded and honours the abort word, so a grid
@@ -48,21 +65,33 @@ namespace {
 constexpr int kWaves = kBfsThreads / 64;
 constexpr int K = kBfsChunkEdges;
 constexpr int kPer = K / kBfsThreads;  // edges per thread per chunk
+constexpr int kWidePer = 4;             // edges per thread at a time in wide levels
+constexpr int kWideChunks = kWidePer / kPer;  // chunks a workgroup takes at a time there
+constexpr int KW = K * kWideChunks;
+constexpr int kFilter = 16384;          // vertices a workgroup remembers as found
 constexpr int64_t kCountMask = (int64_t(1) << kBfsCountBits) - 1;
 constexpr int kBarrierWords = 4;
-constexpr int kGatherPer = kBfsMaxGrid / kBfsThreads;  // arrivals gathered per thread of workgroup 0
-constexpr int kGatherBatch = 1;
+constexpr int kGatherPer = (kBfsMaxGrid + kBfsThreads - 1) / kBfsThreads;  // arrivals gathered per thread of workgroup 0
+constexpr int kGatherBatch = kGatherPer < 4 ? kGatherPer : 4;  // arrivals in flight per thread
 constexpr int kFoldBatch = 1;  // chunk values in flight per thread in the window sum
 
+// Vertex and edge counts of a workgroup's vertices packed in 64 bits: at most
+// eight vertices per thread, at most 2^42 edges.
+constexpr int kTileBits = 14;
+constexpr int64_t kTileMask = (int64_t(1) << kTileBits) - 1;
+static_assert(8 * kBfsThreads <= kTileMask, "the vertices fit their field");
+
 struct BfsShared {
-    int64_t eo[K + 2];       // edge offsets of the chunk's vertices; eo[n] is a sentinel
-    int64_t shift[K + 1];    // row start - edge offset: edge index = rank + shift
-    int32_t u[K + 1];        // the chunk's vertices
+    int64_t shift[KW];       // of the chunk's vertices: edge index = rank in the chunk + shift
+    int32_t u[KW];           // the chunk's vertices
+    uint64_t heads[2][KW / 64];  // one bit per rank: a vertex's first (the buffer not in use is clear)
+    int32_t filter[kFilter];    // filter[v mod kFilter] = v: v is found (-1: none)
     int32_t stage[2][K];     // discovered vertices that have edges: the chunk being
                              // claimed and the one waiting to be placed
     int64_t wave_tot[kWaves];
     uint64_t found_e;        // edges of the staged vertices
     uint32_t found;          // staged vertices
+    uint32_t found2[2];      // vertices found by a solo level, alternating
     uint32_t found_all;      // vertices this workgroup discovered in the current level
     uint32_t bad;            // malformed entries this workgroup met
     int32_t ok;
@@ -74,6 +103,14 @@ struct BfsShared {
 __device__ __forceinline__ uint32_t lanes_before(uint64_t mask)
 {
     return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
+}
+
+// A value that is the same in every lane, kept in scalar registers (the
+// compiler cannot see that one read from LDS or a table is).
+template <class T>
+__device__ __forceinline__ T uniform(const T& v)
+{
+    return read_lane(v, 0);
 }
 
 __device__ __forceinline__ void give_up(const BfsArgs& a, uint32_t tag)
@@ -106,23 +143,9 @@ __device__ __forceinline__ int64_t block_exclusive_sum(int64_t v, BfsShared& s, 
         before += (k < wave) ? t : 0;
         all += t;
     }
-    *total = all;
+    *total = uniform(all);
     __syncthreads();
     return before + inc - v;
-}
-
-// The chunk vertex that owns flat edge rank r: the last k < n with eo[k] <= r.
-__device__ __forceinline__ int owner_of(const BfsShared& s, int n, int64_t r)
-{
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s.eo[mid] <= r)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
 }
 
 // Sum of the packed values of chunks [lo, lo + cnt) (cnt < kBfsMaxGrid),
@@ -170,9 +193,9 @@ __device__ __forceinline__ int64_t block_window_sum(const BfsArgs& a, BfsShared&
         all += s.gather[k][0];
         all_ok = all_ok && s.gather[k][3] != 0;
     }
-    ok = all_ok;
+    ok = uniform(int(all_ok)) != 0;
     __syncthreads();
-    return all;
+    return uniform(all);
 }
 
 // Grid barrier over flag words.  Every workgroup publishes the four 32-bit
@@ -181,7 +204,7 @@ __device__ __forceinline__ int64_t block_window_sum(const BfsArgs& a, BfsShared&
 // publishes the sums, which every workgroup reads into s.res.  Writes made
 // before the call are visible to every workgroup after it.  Returns false
 // if a wait gave up.
-__device__ bool grid_barrier(const BfsArgs& a, BfsShared& s, uint32_t tag, const uint32_t (&v)[kBarrierWords])
+__device__ __forceinline__ bool grid_barrier(const BfsArgs& a, BfsShared& s, uint32_t tag, const uint32_t (&v)[kBarrierWords])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     static_assert(kGatherPer * kBfsThreads >= kBfsMaxGrid, "workgroup 0 gathers the whole grid");
@@ -276,7 +299,533 @@ __device__ bool grid_barrier(const BfsArgs& a, BfsShared& s, uint32_t tag, const
         s.res[3] = uint32_t(w[3]);
     }
     __syncthreads();
-    return s.ok != 0;
+    return uniform(s.ok) != 0;
+}
+
+// The frontier of one level: f vertices with their edge offsets and first
+// edges, D edges in nc chunks, and the vertex of each chunk's first edge.
+struct Frontier {
+    const int32_t* vertex;
+    const int64_t* edge_off;
+    const int64_t* edge_shift;
+    const int32_t* chunk_first;
+    int64_t f, D, nc;
+};
+struct ChunkRange {
+    int64_t k0;  // the chunk's first frontier vertex
+    int n;       // frontier vertices its ranks fall in
+};
+struct FrontierEntry {
+    int64_t off, shift;
+    int32_t u;
+};
+
+// The table entries of the G chunks from c on, as loaded: waited for where
+// frontier_range reads them.
+struct ChunkHead {
+    int32_t first, last;
+};
+template <int G>
+__device__ __forceinline__ ChunkHead chunk_head(const Frontier& fr, int64_t c)
+{
+    return ChunkHead{fr.chunk_first[c], (c + G < fr.nc) ? fr.chunk_first[c + G] : int32_t(fr.f - 1)};
+}
+template <int G>
+__device__ __forceinline__ ChunkRange frontier_range(const Frontier& fr, const ChunkHead& h)
+{
+    int64_t k0 = uniform(h.first);
+    int64_t kend = uniform(h.last);
+    k0 = (k0 < 0) ? 0 : (k0 >= fr.f ? fr.f - 1 : k0);  // memory guards: the table is consistent
+    kend = (kend < k0) ? k0 : (kend >= fr.f ? fr.f - 1 : kend);
+    if (kend - k0 > G * K) kend = k0 + G * K;
+    return ChunkRange{k0, int(kend - k0 + 1)};
+}
+
+// Edges of the G chunks from c on (the last ones may be short).
+template <int G>
+__device__ __forceinline__ int chunk_edges(const Frontier& fr, int64_t c)
+{
+    return int((fr.D - c * K < G * K) ? fr.D - c * K : G * K);
+}
+
+// This thread's first entry of the range (few chunks have more vertices than threads).
+__device__ __forceinline__ FrontierEntry frontier_entry(const Frontier& fr, const ChunkRange& r)
+{
+    const int64_t j = r.k0 + ((int(threadIdx.x) < r.n) ? int(threadIdx.x) : r.n - 1);
+    return FrontierEntry{fr.edge_off[j], fr.edge_shift[j], fr.vertex[j]};
+}
+
+// Entry j of a chunk into LDS: a vertex whose first rank in the chunk is
+// `rank` and first edge there rank + shift.
+__device__ __forceinline__ void put_entry(BfsShared& s, int hb, int j, int rank, int64_t shift, int32_t u)
+{
+    s.shift[j] = shift;
+    s.u[j] = u;
+    atomicOr(reinterpret_cast<unsigned long long*>(&s.heads[hb][rank >> 6]), 1ull << (rank & 63));
+}
+
+// The frontier vertices of the G chunks from c on into LDS (first: this
+// thread's first entry).  The workgroup synchronises before it reads them.
+template <int G>
+__device__ __forceinline__ void frontier_to_lds(const Frontier& fr, BfsShared& s, int hb, int64_t c,
+                                                const ChunkRange& r, const FrontierEntry& first)
+{
+    auto put = [&](int j, const FrontierEntry& e) {
+        const int64_t at = e.off - c * K;
+        if (at < G * K) put_entry(s, hb, j, (at < 0) ? 0 : int(at), e.shift + c * K, e.u);
+    };
+    int j = threadIdx.x;
+    if (j < r.n) put(j, first);
+    for (j += kBfsThreads; j < r.n; j += kBfsThreads)
+        put(j, FrontierEntry{fr.edge_off[r.k0 + j], fr.edge_shift[r.k0 + j], fr.vertex[r.k0 + j]});
+}
+
+// Each thread's ranks of a chunk of cnt edges, whose vertices are in LDS, to
+// their edges: edge index and vertex (u = -1: past the last edge, or an edge
+// outside the graph).  The vertex of a rank is the number of heads at or
+// before it: a wave's row of ranks is one 64-bit word of heads, so that is a
+// count of the heads in the words before and a bit count below the lane (a
+// binary search of the chunk's vertices took a third of the kernel's VALU
+// instructions).  Clears the other buffer of heads.
+template <int PER>
+__device__ __forceinline__ void map_ranks(const BfsArgs& a, BfsShared& s, int hb, int cnt, int64_t (&e)[PER],
+                                          int32_t (&u)[PER])
+{
+    constexpr int kWords = PER * kWaves;        // of heads, one per wave-row
+    constexpr int kHold = (kWords + 63) / 64;   // words held per lane: word 64q + lane
+    const int lane = threadIdx.x & 63, wave = uniform(int(threadIdx.x) >> 6);
+    uint64_t word[kHold];
+    int32_t before[kHold], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kHold; ++q) {
+        word[q] = (64 * q + lane < kWords) ? s.heads[hb][64 * q + lane] : 0u;
+        const int32_t heads = __builtin_popcountll(word[q]);
+        const int32_t inc = wave_inclusive_scan<AddI32>(heads);
+        before[q] = sum + inc - heads;
+        sum += read_lane(inc, 63);
+    }
+    for (int j = threadIdx.x; j < KW / 64; j += kBfsThreads) s.heads[hb ^ 1][j] = 0;
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        const int r = p * kBfsThreads + int(threadIdx.x);
+        constexpr int kRows = 64 / kWaves;  // wave-rows whose words one register holds
+        static_assert(64 % kWaves == 0, "whole rows per register");
+        const int at = (p % kRows) * kWaves + wave;
+        const uint64_t w = read_lane(word[p / kRows], at);
+        const uint32_t k0 = uint32_t(read_lane(before[p / kRows], at)) + uint32_t(w & 1u) - 1u;
+        const uint32_t kr = k0 + lanes_before(w >> 1);
+        const uint32_t k = (kr < uint32_t(KW)) ? kr : uint32_t(KW - 1);  // memory guard: rank 0 has a head
+        e[p] = 0;
+        u[p] = -1;
+        if (r < cnt) {
+            e[p] = r + s.shift[k];
+            if (uint64_t(e[p]) < uint64_t(a.ne))
+                u[p] = s.u[k];
+            else
+                atomicAdd(&s.bad, 1u);
+        }
+    }
+}
+
+// Chunk-table entries of a frontier vertex at `pos` whose edges have ranks
+// [eoff, eoff + d) (on: this lane has one): every chunk that starts in that
+// range.  Called by whole waves: the long runs of a hub are written by all
+// lanes.
+__device__ __forceinline__ void fill_chunk_table(int32_t* table, int64_t cap, bool on, int64_t pos, int64_t eoff,
+                                                 int64_t d)
+{
+    constexpr int kOwn = 4;  // entries a lane writes by itself
+    const int lane = threadIdx.x & 63;
+    const int64_t b0 = (eoff + K - 1) / K;
+    int64_t b1 = on ? (eoff + d + K - 1) / K : b0;
+    if (b1 > cap) b1 = cap;
+    for (int i = 0; i < kOwn; ++i)
+        if (b0 + i < b1) table[b0 + i] = int32_t(pos);
+    uint64_t m = __ballot(b1 - b0 > kOwn);
+    while (m) {
+        const int l = __builtin_ctzll(m);
+        m &= m - 1;
+        const int64_t lo = read_lane(b0, l) + kOwn, hi = read_lane(b1, l);
+        const int32_t at = read_lane(int32_t(pos), l);
+        for (int64_t b = lo + lane; b < hi; b += 64) table[b] = at;
+    }
+}
+
+// One wide level: every edge's endpoint is marked with a plain byte store and
+// the next frontier is gathered by a sweep over the marks, so that no edge
+// pays for an atomic.
+//   expand  every edge whose endpoint is neither in the workgroup's filter of
+//           vertices known to be found (LDS; an R-MAT graph's hubs: 1015 ->
+//           975 us a search) nor settled (a bitmap that no level writes while
+//           it reads it: 1400 -> 1340 us) reads the byte of its endpoint and,
+//           if that is 0, stores 1 and the parent; several edges may find one
+//           vertex and store the same byte and one of its valid parents;
+//   sweep   (after a grid barrier) every workgroup takes an equal run of
+//           vertices, counts those marked but not settled and their edges,
+//           publishes the two sums, adds up what the workgroups before it
+//           published, and writes its vertices' levels and frontier entries
+//           behind them; the vertices become settled.
+// *out_n, *out_e and *found get this workgroup's frontier vertices, their
+// edges and its vertices found; tag advances by one for the inner barrier.
+// Returns false if a wait gave up.
+__device__ __forceinline__ bool wide_level(const BfsArgs& a, BfsShared& s, const Frontier& fr, uint32_t& tag, int& hb,
+                                           int32_t lev, int64_t* out_n, int64_t* out_e, uint32_t* found)
+{
+    const int64_t nc = fr.nc;
+    const int q = lev & 1;
+    auto load_entry = [&](const ChunkRange& r) { return frontier_entry(fr, r); };
+    auto store_chunk = [&](int64_t c, const ChunkRange& r, const FrontierEntry& e0) {
+        frontier_to_lds<kWideChunks>(fr, s, hb, c, r, e0);
+    };
+    // the endpoints of each thread's ranks of chunk c and the vertices they leave (-1: no edge)
+    auto load_ends = [&](int64_t c, int32_t (&v)[kWidePer], int32_t (&u)[kWidePer]) {
+        int64_t e[kWidePer];
+        map_ranks(a, s, hb, chunk_edges<kWideChunks>(fr, c), e, u);
+        hb ^= 1;
+#pragma unroll
+        for (int p = 0; p < kWidePer; ++p) v[p] = (u[p] >= 0) ? __builtin_nontemporal_load(a.col + e[p]) : -1;
+    };
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t B = gridDim.x, wg = blockIdx.x;
+    const int64_t V = a.nv;
+
+    const int64_t first = wg * kWideChunks, step = B * kWideChunks;
+    if (first < nc) {
+        // Software pipeline: while chunk c's marks are on their way, the
+        // frontier entries of this workgroup's next chunk are fetched, its ranks
+        // mapped and its column loads issued; the table entries that name the
+        // chunk after that are fetched one step earlier still.
+        ChunkRange next = frontier_range<kWideChunks>(fr, chunk_head<kWideChunks>(fr, first));
+        FrontierEntry fe = load_entry(next);
+        ChunkHead after{};
+        if (first + step < nc) after = chunk_head<kWideChunks>(fr, first + step);
+        store_chunk(first, next, fe);
+        __syncthreads();
+        int32_t v[kWidePer], u[kWidePer];
+        load_ends(first, v, u);
+        // the edges of the chunk before whose endpoints were not settled, and their marks
+        int32_t pv[kWidePer], pu[kWidePer];
+        uint8_t mark[kWidePer];
+#pragma unroll
+        for (int p = 0; p < kWidePer; ++p) pv[p] = -1;
+        auto store_marks = [&]() {
+#pragma unroll
+            for (int p = 0; p < kWidePer; ++p) {
+                if (pv[p] < 0) continue;
+                s.filter[pv[p] & (kFilter - 1)] = pv[p];
+                if (mark[p] == 0) {
+                    a.found[pv[p]] = 1;
+                    if (a.parent) a.parent[pv[p]] = pu[p];
+                }
+            }
+        };
+        for (int64_t c = first;; c += step) {
+            const bool more = c + step < nc;
+            if (more) {
+                next = frontier_range<kWideChunks>(fr, after);
+                fe = load_entry(next);
+                if (c + 2 * step < nc) after = chunk_head<kWideChunks>(fr, c + 2 * step);
+            }
+            uint8_t bits[kWidePer];
+#pragma unroll
+            for (int p = 0; p < kWidePer; ++p) {
+                if (uint32_t(v[p]) >= uint32_t(V)) {
+                    if (u[p] >= 0) atomicAdd(&s.bad, 1u);
+                    v[p] = -1;
+                }
+                if (v[p] >= 0 && s.filter[v[p] & (kFilter - 1)] == v[p]) v[p] = -1;
+                bits[p] = (v[p] < 0) ? uint8_t(0xff) : a.settled[v[p] >> 3];
+            }
+            store_marks();
+            int32_t v2[kWidePer], u2[kWidePer];
+            if (more) {
+                __syncthreads();  // chunk c's entries were read
+                store_chunk(c + step, next, fe);
+                __syncthreads();
+                load_ends(c + step, v2, u2);
+            }
+#pragma unroll
+            for (int p = 0; p < kWidePer; ++p) {
+                const bool open = !((bits[p] >> (v[p] & 7)) & 1u);
+                pv[p] = v[p];
+                pu[p] = u[p];
+                mark[p] = open ? a.found[v[p]] : uint8_t(1);  // a stale 0 only costs the stores again
+            }
+            if (!more) break;
+#pragma unroll
+            for (int p = 0; p < kWidePer; ++p) {
+                v[p] = v2[p];
+                u[p] = u2[p];
+            }
+        }
+        store_marks();
+    }
+    const uint32_t v0[kBarrierWords] = {0u, 0u, 0u, 0u};
+    if (!grid_barrier(a, s, tag, v0)) return false;
+    ++tag;
+
+    // the sweep, in groups of eight vertices (one byte of settled bits): this workgroup's run [g0, g1)
+    const int64_t groups = (V + 7) / 8;
+    const int64_t run = (groups + B - 1) / B;
+    const int64_t g0 = (wg * run < groups) ? wg * run : groups;
+    const int64_t g1 = (g0 + run < groups) ? g0 + run : groups;
+    // the new vertices of group i (i < g1) as a bit mask; *was: the settled ones
+    auto load_new = [&](int64_t i, uint32_t* was) -> uint32_t {
+        *was = 0xffu;
+        if (i >= g1) return 0u;
+        const uint64_t m = reinterpret_cast<const uint64_t*>(a.found)[i];  // eight bytes, each 0 or 1
+        *was = a.settled[i];
+        return uint32_t((m * 0x0102040810204080ull) >> 56) & ~*was;
+    };
+    auto load_rows = [&](int64_t i, uint32_t fresh, int64_t (&row)[9]) {
+#pragma unroll
+        for (int j = 0; j < 9; ++j) row[j] = fresh ? a.row[(8 * i + j < V) ? 8 * i + j : V] : 0;
+    };
+    auto degree = [&](const int64_t (&row)[9], int j) -> int64_t {  // -1: not inside [0, E]
+        return (row[j] >= 0 && row[j + 1] >= row[j] && row[j + 1] <= a.ne) ? row[j + 1] - row[j] : -1;
+    };
+    int64_t n = 0, e = 0;
+    uint32_t all = 0;
+    for (int64_t t0 = g0; t0 < g1; t0 += kBfsThreads) {
+        int64_t row[9];
+        uint32_t was;
+        const uint32_t fresh = load_new(t0 + tid, &was);
+        load_rows(t0 + tid, fresh, row);
+        all += uint32_t(__builtin_popcount(fresh));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if ((fresh >> j) & 1u) {
+                const int64_t d = degree(row, j);
+                if (d < 0) atomicAdd(&s.bad, 1u);
+                n += (d > 0) ? 1 : 0;
+                e += (d > 0) ? d : 0;
+            }
+        }
+    }
+    // workgroup sums, published at once
+    n = read_lane(wave_inclusive_scan<AddI64>(n), 63);
+    e = read_lane(wave_inclusive_scan<AddI64>(e), 63);
+    const int64_t f = read_lane(wave_inclusive_scan<AddI64>(int64_t(all)), 63);
+    if (lane == 0) {
+        s.gather[wave][0] = n;
+        s.gather[wave][1] = e;
+        s.gather[wave][2] = f;
+    }
+    __syncthreads();
+    n = e = 0;
+    all = 0;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        n += s.gather[k][0];
+        e += s.gather[k][1];
+        all += uint32_t(s.gather[k][2]);
+    }
+    if (tid == 0) {
+        const uint32_t out[3] = {uint32_t(n), uint32_t(uint64_t(e)), uint32_t(uint64_t(e) >> 32)};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) slot_store(a.swept + 4 * wg + k, (uint64_t(tag) << 32) | out[k]);
+    }
+    __syncthreads();  // s.gather is read before it is written again
+    *out_n = uniform(n);
+    *out_e = uniform(e);
+    *found = uniform(all);
+
+    // what the workgroups before this one found: four of them in flight per thread
+    int64_t p_n = 0, p_e = 0;
+    bool ok = true;
+    constexpr int kBatch = kGatherBatch;
+    for (int64_t j0 = 0; j0 < wg; j0 += kBatch * kBfsThreads) {
+        uint64_t w[kBatch][3];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int64_t j = j0 + i * kBfsThreads + tid;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) w[i][k] = (j < wg) ? slot_load(a.swept + 4 * j + k) : (uint64_t(tag) << 32);
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int64_t j = j0 + i * kBfsThreads + tid;
+            if (j < wg) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    w[i][k] = await_word(a.swept + 4 * j + k, w[i][k], tag, a.spin_limit, a.abort_word, ok);
+            }
+            p_n += uint32_t(w[i][0]);
+            p_e += int64_t(uint64_t(uint32_t(w[i][1])) | (uint64_t(uint32_t(w[i][2])) << 32));
+        }
+    }
+    const bool wave_ok = __ballot(!ok) == 0;
+    p_n = read_lane(wave_inclusive_scan<AddI64>(p_n), 63);
+    p_e = read_lane(wave_inclusive_scan<AddI64>(p_e), 63);
+    if (lane == 0) {
+        s.gather[wave][0] = p_n;
+        s.gather[wave][1] = p_e;
+        s.gather[wave][3] = wave_ok ? 1 : 0;
+    }
+    __syncthreads();
+    p_n = p_e = 0;
+    ok = true;
+#pragma unroll
+    for (int k = 0; k < kWaves; ++k) {
+        p_n += s.gather[k][0];
+        p_e += s.gather[k][1];
+        ok = ok && s.gather[k][3] != 0;
+    }
+    p_n = uniform(p_n);
+    p_e = uniform(p_e);
+    __syncthreads();
+    if (uniform(int(ok)) == 0) {
+        if (tid == 0) give_up(a, tag);
+        return false;
+    }
+
+    // the run's new vertices: levels, frontier entries, the next level's chunk table
+    int32_t* nxt = a.queue[q ^ 1];
+    int64_t* nxt_eo = a.edge_off[q ^ 1];
+    int64_t* nxt_sh = a.edge_shift[q ^ 1];
+    int32_t* nxt_cf = a.chunk_first[q ^ 1];
+    for (int64_t t0 = g0; t0 < g1; t0 += kBfsThreads) {
+        const int64_t i = t0 + tid;
+        int64_t row[9];
+        uint32_t was;
+        const uint32_t fresh = load_new(i, &was);
+        load_rows(i, fresh, row);
+        int64_t mine = 0;  // edges << kTileBits | vertices
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if ((fresh >> j) & 1u) {
+                const int64_t d = degree(row, j);
+                mine += (d > 0) ? ((d << kTileBits) | 1) : 0;
+            }
+        }
+        int64_t tot = 0;
+        const int64_t before = block_exclusive_sum(mine, s, &tot);
+        int64_t pos = p_n + (before & kTileMask), eoff = p_e + (before >> kTileBits);
+        p_n += tot & kTileMask;
+        p_e += tot >> kTileBits;
+        if (__ballot(fresh != 0) == 0) continue;
+        if (fresh) a.settled[i] = uint8_t(was | fresh);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const bool on = ((fresh >> j) & 1u) != 0;
+            const int64_t v = 8 * i + j;
+            if (on) a.level[v] = lev + 1;
+            const int64_t d = on ? degree(row, j) : 0;
+            const bool queued = d > 0 && pos < V;
+            if (queued) {
+                nxt[pos] = int32_t(v);
+                nxt_eo[pos] = eoff;
+                nxt_sh[pos] = row[j] - eoff;
+            }
+            fill_chunk_table(nxt_cf, a.chunk_cap, queued, pos, eoff, d);
+            if (d > 0) {
+                ++pos;
+                eoff += d;
+            }
+        }
+    }
+    return true;
+}
+
+// Levels of at most K edges, run by one workgroup from the frontier in
+// global memory: the next frontier stays in LDS, and a level is the chain
+// column, claim, row range (four round trips with the frontier kept in
+// memory and a grid barrier after each level).  Stops at a frontier of more
+// edges, at an empty one, or after kSoloLevels (the other workgroups wait in
+// the barrier meanwhile, and every wait is bounded).
+constexpr int kSoloLevels = 32;
+struct SoloResult {
+    int64_t n, e;        // the next frontier (written to global memory)
+    int64_t reached, scanned;
+    int32_t levels;      // levels that found a vertex
+    int32_t steps;       // levels run
+};
+__device__ __forceinline__ SoloResult solo_levels(const BfsArgs& a, BfsShared& s, int& hb, int32_t lev, int64_t f,
+                                                  int64_t D)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t V = a.nv;
+    SoloResult out{};
+    for (int j = tid; j < f; j += kBfsThreads) {
+        const int64_t at = a.edge_off[lev & 1][j];
+        if (j < K && at >= 0 && at < K) put_entry(s, hb, j, int(at), a.edge_shift[lev & 1][j], a.queue[lev & 1][j]);
+    }
+    if (tid == 0) s.found2[0] = 0;
+    __syncthreads();
+    for (;;) {
+        out.scanned += D;
+        int64_t e[kPer];
+        int32_t u[kPer], v[kPer];
+        map_ranks(a, s, hb, int(D), e, u);
+        hb ^= 1;
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) v[p] = (u[p] >= 0) ? a.col[e[p]] : -1;
+        bool win[kPer];
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            win[p] = false;
+            if (uint32_t(v[p]) < uint32_t(V)) {
+                const uint32_t mask = 1u << (8 * (v[p] & 3));
+                win[p] = !(atomicOr(reinterpret_cast<uint32_t*>(a.found) + (v[p] >> 2), mask) & mask);
+            } else if (u[p] >= 0) {
+                atomicAdd(&s.bad, 1u);
+            }
+        }
+        int64_t d[kPer], beg[kPer];
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            d[p] = beg[p] = 0;
+            if (win[p]) d[p] = row_range(a, v[p], &beg[p]);
+        }
+        int64_t mine = 0;  // edges << kTileBits | vertices
+        uint32_t all = 0;
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            if (win[p]) {
+                atomicOr(reinterpret_cast<uint32_t*>(a.settled) + (v[p] >> 5), 1u << (v[p] & 31));
+                a.level[v[p]] = lev + out.steps + 1;
+                if (a.parent) a.parent[v[p]] = u[p];
+                if (d[p] < 0) atomicAdd(&s.bad, 1u);
+                mine += (d[p] > 0) ? ((d[p] << kTileBits) | 1) : 0;
+            }
+            all += uint32_t(__popcll(__ballot(win[p])));
+        }
+        const int slot = out.steps & 1;
+        if (lane == 0 && all) atomicAdd(&s.found2[slot], all);
+        int64_t tot = 0;
+        const int64_t before = block_exclusive_sum(mine, s, &tot);
+        const uint32_t found = uniform(s.found2[slot]);
+        if (tid == 0) s.found2[slot ^ 1] = 0;
+        int64_t pos = before & kTileMask, eoff = before >> kTileBits;
+        out.n = tot & kTileMask;
+        out.e = tot >> kTileBits;
+        ++out.steps;
+        out.levels += (found > 0) ? 1 : 0;
+        out.reached += found;
+        const bool stay = out.n > 0 && out.e <= K && out.steps < kSoloLevels;
+        const int q = (lev + out.steps) & 1;
+#pragma unroll
+        for (int p = 0; p < kPer; ++p) {
+            const bool queued = d[p] > 0;
+            if (stay) {
+                if (queued) put_entry(s, hb, int(pos), int(eoff), beg[p] - eoff, v[p]);
+            } else {
+                if (queued) {
+                    a.queue[q][pos] = v[p];
+                    a.edge_off[q][pos] = eoff;
+                    a.edge_shift[q][pos] = beg[p] - eoff;
+                }
+                fill_chunk_table(a.chunk_first[q], a.chunk_cap, queued, pos, eoff, d[p]);
+            }
+            if (queued) {
+                ++pos;
+                eoff += d[p];
+            }
+        }
+        if (!stay) return out;
+        D = out.e;
+        __syncthreads();
+    }
 }
 
 __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
@@ -297,14 +846,38 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
     // that overlap would break the bound of the chunk tables, so such a
     // graph is not searched.
     int64_t src_beg = 0;
-    const int64_t src_deg = row_range(a, a.src, &src_beg);
+    const int64_t src_deg = uniform(row_range(a, a.src, &src_beg));
+    src_beg = uniform(src_beg);
     uint32_t decreasing = 0;
-    for (int64_t v = wg * kBfsThreads + tid; v < V; v += B * kBfsThreads) {
-        const bool is_src = (v == a.src);
-        if ((v & 31) == 0) a.visited[v >> 5] = ((a.src >> 5) == (v >> 5)) ? (1u << (a.src & 31)) : 0u;
-        a.level[v] = is_src ? 0 : -1;
-        if (a.parent) a.parent[v] = is_src ? a.src : -1;
-        decreasing += (a.row[v] > a.row[v + 1]) ? 1u : 0u;
+    constexpr int kInit = 4;  // vertices per thread in flight
+    for (int64_t v0 = wg * kBfsThreads + tid; v0 < V; v0 += kInit * B * kBfsThreads) {
+        int64_t r0[kInit], r1[kInit];
+#pragma unroll
+        for (int k = 0; k < kInit; ++k) {
+            const int64_t v = v0 + k * B * kBfsThreads;
+            r0[k] = (v < V) ? a.row[v] : 0;
+            r1[k] = (v < V) ? a.row[v + 1] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kInit; ++k) {
+            const int64_t v = v0 + k * B * kBfsThreads;
+            if (v >= V) break;
+            const bool is_src = (v == a.src);
+            a.level[v] = is_src ? 0 : -1;
+            if (a.parent) a.parent[v] = is_src ? a.src : -1;
+            decreasing += (r0[k] > r1[k]) ? 1u : 0u;
+        }
+    }
+    const int64_t groups = (V + 7) / 8;
+    for (int64_t i = wg * kBfsThreads + tid; i < groups; i += B * kBfsThreads) {
+        // vertices past the last one count as found
+        uint32_t b = (8 * i + 8 > V) ? 0xffu << uint32_t(V - 8 * i) & 0xffu : 0u;
+        if ((a.src >> 3) == i) b |= 1u << (a.src & 7);
+        uint64_t m = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m |= uint64_t((b >> j) & 1u) << (8 * j);
+        reinterpret_cast<uint64_t*>(a.found)[i] = m;
+        a.settled[i] = uint8_t(b);
     }
     const int64_t d0 = (src_deg > 0) ? src_deg : 0;
     if (wg == 0 && tid == 0 && d0 > 0) {
@@ -314,6 +887,9 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
     }
     for (int64_t b = wg * kBfsThreads + tid; b * K < d0 && b < a.chunk_cap; b += B * kBfsThreads)
         a.chunk_first[0][b] = 0;
+    for (int j = tid; j < KW / 64; j += kBfsThreads) s.heads[0][j] = s.heads[1][j] = 0;
+    for (int j = tid; j < kFilter; j += kBfsThreads) s.filter[j] = -1;
+    int hb = 0;  // the buffer of heads to be filled next (clear)
     if (tid == 0) {
         s.bad = (wg == 0 && src_deg < 0) ? 1u : 0u;
         s.found_all = 0;
@@ -358,7 +934,43 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
         int32_t* nxt_cf = a.chunk_first[q ^ 1];
         const int64_t nc = (D + K - 1) / K;
         if (nc > a.chunk_cap) break;  // cannot happen with non-decreasing rows (memory guard)
+        if (D <= K) {
+            // few edges: workgroup 0 runs this level, and those after it that are
+            // as small, without a grid barrier between them
+            SoloResult r{};
+            if (wg == 0) r = solo_levels(a, s, hb, lev, f, D);
+            levels += r.levels;
+            reached += r.reached;
+            scanned += r.scanned;
+            const uint32_t vb[kBarrierWords] = {uint32_t(r.n), uint32_t(uint64_t(r.e)), uint32_t(uint64_t(r.e) >> 32),
+                                                uint32_t(r.steps)};
+            ok = grid_barrier(a, s, tag, vb);
+            f = uniform(s.res[0]);
+            D = uniform(s.res[1]);
+            lev += uniform(int32_t(s.res[3]));
+            continue;
+        }
         scanned += D;
+        const Frontier fr{cur, cur_eo, cur_sh, cur_cf, f, D, nc};
+        if (D >= kBfsWideEdges && D >= V / 4) {
+            int64_t out_n = 0, out_e = 0;
+            uint32_t found = 0;
+            ok = wide_level(a, s, fr, tag, hb, lev, &out_n, &out_e, &found);
+            if (!ok) break;
+            const uint32_t vb[kBarrierWords] = {uint32_t(out_n), uint32_t(uint64_t(out_e)),
+                                                uint32_t(uint64_t(out_e) >> 32), found};
+            ok = grid_barrier(a, s, tag, vb);
+            if (!ok) break;
+            f = uniform(s.res[0]);
+            D = uniform(s.res[1]);
+            if (f > V) f = V;  // cannot happen: each vertex is found once (memory guard)
+            if (const int64_t more = uniform(s.res[3])) {
+                ++levels;
+                reached += more;
+            }
+            ++lev;
+            continue;
+        }
         int64_t run_n = 0, run_e = 0;    // offsets through this workgroup's previous chunk
         int64_t mine_n = 0, mine_e = 0;  // what this workgroup placed in this level
         if (tid == 0) s.found_all = 0;
@@ -372,21 +984,9 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
             int64_t A_n = 0, A_e = 0;  // the claimed chunk's staged vertices and their edges
             if (have) {
                 // (a) the chunk's frontier vertices
-                const int64_t r_lo = c * K;
-                const int64_t r_hi = (D - r_lo < K) ? D : r_lo + K;
-                int64_t k0 = cur_cf[c];
-                int64_t kend = (c + 1 < nc) ? int64_t(cur_cf[c + 1]) : f - 1;
-                k0 = (k0 < 0) ? 0 : (k0 >= f ? f - 1 : k0);  // memory guards: the table is consistent
-                kend = (kend < k0) ? k0 : (kend >= f ? f - 1 : kend);
-                if (kend - k0 > K) kend = k0 + K;
-                const int n = int(kend - k0 + 1);
-                for (int j = tid; j < n; j += kBfsThreads) {
-                    s.eo[j] = cur_eo[k0 + j];
-                    s.shift[j] = cur_sh[k0 + j];
-                    s.u[j] = cur[k0 + j];
-                }
+                const ChunkRange cr = frontier_range<1>(fr, chunk_head<1>(fr, c));
+                frontier_to_lds<1>(fr, s, hb, c, cr, frontier_entry(fr, cr));
                 if (tid == 0) {
-                    s.eo[n] = INT64_MAX;
                     s.found = 0;
                     s.found_e = 0;
                 }
@@ -397,39 +997,32 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
                 int64_t e[kPer];
                 int32_t u[kPer];
                 bool act[kPer];
+                map_ranks(a, s, hb, chunk_edges<1>(fr, c), e, u);
+                hb ^= 1;
 #pragma unroll
-                for (int p = 0; p < kPer; ++p) {
-                    const int64_t r = r_lo + int64_t(p) * kBfsThreads + tid;
-                    act[p] = false;
-                    e[p] = 0;
-                    u[p] = -1;
-                    if (r < r_hi) {
-                        const int kk = owner_of(s, n, r);
-                        e[p] = r + s.shift[kk];
-                        u[p] = s.u[kk];
-                        act[p] = (e[p] >= 0 && e[p] < a.ne);
-                        if (!act[p]) atomicAdd(&s.bad, 1u);
-                    }
-                }
+                for (int p = 0; p < kPer; ++p) act[p] = u[p] >= 0;
                 int32_t v[kPer];
 #pragma unroll
                 for (int p = 0; p < kPer; ++p) v[p] = act[p] ? a.col[e[p]] : -1;
-                uint32_t bits[kPer];
+                uint8_t seen[kPer];
 #pragma unroll
                 for (int p = 0; p < kPer; ++p) {
                     if (act[p] && uint32_t(v[p]) >= uint32_t(V)) {
                         atomicAdd(&s.bad, 1u);
                         act[p] = false;
                     }
-                    bits[p] = act[p] ? a.visited[v[p] >> 5] : ~0u;  // a stale clear bit only costs an atomic
+                    seen[p] = act[p] ? a.found[v[p]] : uint8_t(1);  // a stale 0 only costs an atomic
                 }
                 bool win[kPer];
 #pragma unroll
                 for (int p = 0; p < kPer; ++p) {
-                    const uint32_t mask = 1u << (v[p] & 31);
                     win[p] = false;
-                    if (act[p] && !(bits[p] & mask))
-                        win[p] = !(atomicOr(a.visited + (v[p] >> 5), mask) & mask);
+                    if (!seen[p]) {
+                        const uint32_t mask = 1u << (8 * (v[p] & 3));
+                        win[p] = !(atomicOr(reinterpret_cast<uint32_t*>(a.found) + (v[p] >> 2), mask) & mask);
+                    }
+                    if (win[p])
+                        atomicOr(reinterpret_cast<uint32_t*>(a.settled) + (v[p] >> 5), 1u << (v[p] & 31));
                 }
                 int64_t dv[kPer];
 #pragma unroll
@@ -464,8 +1057,8 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
                     }
                 }
                 __syncthreads();
-                A_n = s.found;
-                A_e = int64_t(s.found_e);
+                A_n = uniform(s.found);
+                A_e = uniform(int64_t(s.found_e));
 
                 // (c) publish (edges, vertices) packed, at once
                 if (wave == 0) publish_slot(a.slots + 2 * c, (A_e << kBfsCountBits) | A_n, tag, lane);
@@ -521,17 +1114,15 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
 #pragma unroll
                 for (int t = 0; t < kPer; ++t) {
                     const int j = tid * kPer + t;
-                    if (j < prev_n) {
-                        const int64_t pos = p_n + j;
-                        if (pos < V) {
-                            nxt[pos] = vl[t];
-                            nxt_eo[pos] = eoff;
-                            nxt_sh[pos] = bl[t] - eoff;
-                            for (int64_t b = (eoff + K - 1) / K; b * K < eoff + dl[t] && b < a.chunk_cap; ++b)
-                                nxt_cf[b] = int32_t(pos);
-                        }
-                        eoff += dl[t];
+                    const int64_t pos = p_n + j;
+                    const bool queued = j < prev_n && pos < V;
+                    if (queued) {
+                        nxt[pos] = vl[t];
+                        nxt_eo[pos] = eoff;
+                        nxt_sh[pos] = bl[t] - eoff;
                     }
+                    fill_chunk_table(nxt_cf, a.chunk_cap, queued, pos, eoff, dl[t]);
+                    eoff += dl[t];
                 }
             }
             if (!have) break;
@@ -546,20 +1137,22 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
                                             uint32_t(uint64_t(mine_e) >> 32), s.found_all};
         ok = grid_barrier(a, s, tag, vb);
         if (!ok) break;
-        f = s.res[0];
-        D = s.res[1];
+        f = uniform(s.res[0]);
+        D = uniform(s.res[1]);
         if (f > V) f = V;  // cannot happen: each vertex is claimed once (memory guard)
-        if (s.res[3] > 0) {
+        if (const int64_t more = uniform(s.res[3])) {
             ++levels;
-            reached += s.res[3];
+            reached += more;
         }
         ++lev;
     }
 
-    if (ok && wg == 0 && tid == 0 && a.stats) {
-        int64_t bad = 0;
-        for (int64_t j = 0; j < B; ++j)
-            bad += __hip_atomic_load(a.partial + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ok && wg == 0 && a.stats) {
+        int64_t mine = 0, bad = 0;
+        for (int64_t j = tid; j < B; j += kBfsThreads)
+            mine += __hip_atomic_load(a.partial + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        block_exclusive_sum(mine, s, &bad);
+        if (tid != 0) return;
         a.stats[0] = levels;
         a.stats[1] = reached;
         a.stats[2] = scanned;

@@ -1057,9 +1057,11 @@ struct BfsWorkspace {
     uint64_t* slots = nullptr;
     uint64_t* arrive = nullptr;
     uint64_t* go = nullptr;
+    uint64_t* swept = nullptr;
     uint32_t* abort_word = nullptr;
     int64_t* partial = nullptr;
-    uint32_t* visited = nullptr;
+    uint8_t* found = nullptr;
+    uint8_t* settled = nullptr;
     int64_t* edge_off[2] = {nullptr, nullptr};
     int64_t* edge_shift[2] = {nullptr, nullptr};
     int32_t* queue[2] = {nullptr, nullptr};
@@ -1070,7 +1072,7 @@ std::map<std::pair<int, hipStream_t>, BfsWorkspace> g_bfs_ws;
 
 // Workgroups per CU the search asks for (the occupancy limit and the
 // co-residency test may lower it).
-constexpr int kBfsGroupsPerCu = 4;
+constexpr int kBfsGroupsPerCu = 1;
 
 void free_bfs_workspace(BfsWorkspace& ws)
 {
@@ -1091,9 +1093,13 @@ lscan_status ensure_bfs_workspace(BfsWorkspace& ws, hipStream_t stream, int64_t 
         free_bfs_workspace(ws);
     }
     // flag region first (zeroed), then 8-byte arrays, then 4-byte arrays
-    const size_t flag_words = 2 * size_t(chunks) + 4 * size_t(grid) + 4 + 1;
-    const size_t bytes = flag_words * 8 + size_t(grid) * 8 + size_t(nv) * 8 * 4 + size_t(nv) * 4 * 2 +
-                         size_t(chunks) * 4 * 2 + size_t((nv + 31) / 32) * 4;
+    const size_t flag_words = 2 * size_t(chunks) + 8 * size_t(grid) + 4 + 1;
+    // (the found bytes, padded to 32, are read eight at a time)
+    const size_t tail = flag_words * 8 + size_t(grid) * 8 + size_t(nv) * 8 * 4 + size_t(nv) * 4 * 2 +
+                        size_t(chunks) * 4 * 2;
+    const size_t found_at = (tail + 31) / 32 * 32;
+    const size_t padded = (size_t(nv) + 31) / 32 * 32;
+    const size_t bytes = found_at + padded + padded / 8;
     e = hipMalloc(reinterpret_cast<void**>(&ws.mem), bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -1104,7 +1110,8 @@ lscan_status ensure_bfs_workspace(BfsWorkspace& ws, hipStream_t stream, int64_t 
     ws.slots = w;
     ws.arrive = ws.slots + 2 * chunks;
     ws.go = ws.arrive + 4 * size_t(grid);
-    ws.abort_word = reinterpret_cast<uint32_t*>(ws.go + 4);
+    ws.swept = ws.go + 4;
+    ws.abort_word = reinterpret_cast<uint32_t*>(ws.swept + 4 * size_t(grid));
     ws.flag_bytes = flag_words * 8;
     ws.partial = reinterpret_cast<int64_t*>(w + flag_words);
     ws.edge_off[0] = ws.partial + grid;
@@ -1115,7 +1122,8 @@ lscan_status ensure_bfs_workspace(BfsWorkspace& ws, hipStream_t stream, int64_t 
     ws.queue[1] = ws.queue[0] + nv;
     ws.chunk_first[0] = ws.queue[1] + nv;
     ws.chunk_first[1] = ws.chunk_first[0] + chunks;
-    ws.visited = reinterpret_cast<uint32_t*>(ws.chunk_first[1] + chunks);
+    ws.found = reinterpret_cast<uint8_t*>(ws.mem + found_at);
+    ws.settled = ws.found + padded;
     ws.cap_v = nv;
     ws.cap_chunks = chunks;
     ws.cap_grid = grid;
@@ -1181,8 +1189,9 @@ lscan_status bfs_run(const int64_t* row, const int32_t* col, int64_t nv, int64_t
     BfsWorkspace& bw = g_bfs_ws[std::make_pair(dev, stream)];
     st = ensure_bfs_workspace(bw, stream, nv, chunks, grid);
     if (st != LSCAN_OK) return st;
-    // tags base + 1 .. base + nv + 2: the start barrier and at most nv levels
-    const uint64_t need = uint64_t(nv) + 3;
+    // tags: the start barrier's, one per level (at most nv) and one more per wide
+    // level (the frontiers of all levels together have at most ne edges)
+    const uint64_t need = uint64_t(nv) + 3 + uint64_t(ne / kBfsWideEdges) + 1;
     if (bw.next_tag + need >= uint64_t(UINT32_MAX)) {
         e = hipMemsetAsync(bw.mem, 0, bw.flag_bytes, stream);
         if (e != hipSuccess) return device_error(e);
@@ -1198,7 +1207,8 @@ lscan_status bfs_run(const int64_t* row, const int32_t* col, int64_t nv, int64_t
     a.level = level;
     a.parent = parent;
     a.stats = stats;
-    a.visited = bw.visited;
+    a.found = bw.found;
+    a.settled = bw.settled;
     for (int k = 0; k < 2; ++k) {
         a.queue[k] = bw.queue[k];
         a.edge_off[k] = bw.edge_off[k];
@@ -1210,6 +1220,7 @@ lscan_status bfs_run(const int64_t* row, const int32_t* col, int64_t nv, int64_t
     a.arrive = bw.arrive;
     a.partial = bw.partial;
     a.go = bw.go;
+    a.swept = bw.swept;
     a.abort_word = bw.abort_word;
     a.timeout_flag = ws->ctrl + 2;
     a.ctrl = ws->ctrl;

@@ -295,3 +295,54 @@ def test_full_size_rmat_scale22(gpu_lib):
     check(rh, ch, src, levels.cpu().numpy(), parents.cpu().numpy(), stats.cpu().numpy(), "rmat scale 22")
     del row, col, levels, parents
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("shape", ["random", "ragged", "star", "malformed"])
+def test_wide_levels(gpu_lib, shape):
+    # levels of at least 2^20 edges (and a quarter as many as vertices) are expanded
+    # by marking and gathered by a sweep over the vertices
+    g = np.random.default_rng(41)
+    want_bad = 0
+    if shape == "star":  # the hub's level, then one of as many single-edge vertices
+        nv = (1 << 21) + 3
+        row, col = csr(np.zeros(nv - 1, np.int64), np.arange(1, nv), nv, symmetric=True)
+        src = nv - 1
+    else:
+        # vertex counts that end inside a sweep's group of eight; unreached and edgeless vertices
+        nv = 65_537 if shape == "random" else 4_099
+        s, d = w.uniform_random_edges(nv, (1 << 21) + 5, seed=42)
+        keep = s % 5 != 3
+        row, col = csr(s[keep], d[keep], nv)
+        src = int(np.flatnonzero(np.diff(row))[0])
+    clean_row, clean_col = row, col
+    if shape == "malformed":  # columns outside [0, V) in rows that a wide level expands
+        col = col.copy()
+        pos = np.sort(g.choice(col.shape[0], 64, replace=False))
+        col[pos[:32]] = nv
+        col[pos[32:]] = -1
+        ok = np.ones(col.shape[0], bool)
+        ok[pos] = False
+        src_of = np.repeat(np.arange(nv), np.diff(row))
+        clean_row, clean_col = csr(src_of[ok], col[ok], nv)
+        want_bad = int(np.sum(oracle.bfs_levels(clean_row, clean_col, src)[src_of[pos]] >= 0))
+    log(f"[bfs] wide {shape} V={nv} E={col.shape[0]}")
+    levels, parents, stats = run(gpu_lib, row, col, src)
+    assert int(stats[3]) == want_bad
+    reached = levels >= 0
+    assert int(stats[2]) == int(np.diff(row)[reached].sum())
+    stats[2], stats[3] = int(np.diff(clean_row)[reached].sum()), 0
+    check(clean_row, clean_col, src, levels, parents, stats, f"wide {shape}")
+
+
+@pytest.mark.parametrize("fan", [1, 2047, 2048, 2049, 70_000])
+def test_small_levels_by_one_workgroup(gpu_lib, fan):
+    # a chain longer than one run of small levels, then `fan` edges (around the
+    # largest level that one workgroup runs), whose ends lead to one vertex
+    chain = 70
+    nv = chain + fan + 1
+    s = np.concatenate([np.arange(chain - 1), np.full(fan, chain - 1), np.arange(chain, chain + fan)])
+    d = np.concatenate([np.arange(1, chain), np.arange(chain, chain + fan), np.full(fan, nv - 1)])
+    row, col = csr(s, d, nv)
+    log(f"[bfs] chain and fan {fan}")
+    levels, parents, stats = run(gpu_lib, row, col, 0)
+    check(row, col, 0, levels, parents, stats, f"fan {fan}")
