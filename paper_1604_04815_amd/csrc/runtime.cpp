@@ -156,6 +156,20 @@ int small_array_shape(int64_t bytes)
     return -1;
 }
 
+// The same for segmented scans (device time per launch, int32 add with
+// segments of 24 elements: 2^16 9.7 against 11.4 us at 512 x 8, 2^18 10.1 /
+// 11.7, 2^20 12.1 / 13.2; above 4 MiB of input 512 x 8 is the best shape).
+int small_segmented_shape(int64_t bytes)
+{
+    if (bytes <= (int64_t(1) << 20)) return 6;  // 512 x 2
+    if (bytes <= (int64_t(4) << 20)) return 2;  // 512 x 4
+    return -1;
+}
+
+// Segmented launches of at most this many blocks per workgroup search the
+// offsets for each block instead of reading the table of first segments.
+constexpr int64_t kSearchedBlocks = 2;
+
 lscan_status device_error(hipError_t e)
 {
     t_last_hip_error = int32_t(e);
@@ -699,7 +713,7 @@ int64_t batch_blocks(const KernelEntry& k, const lscan_array& arr, int64_t L)
 // arguments.  Called with g_mu held.  ws_fixed is a workspace owned by a
 // graph, or null for the per-stream one.
 // The parameters a request runs with: the caller's, else the operator's;
-// plain add / max / min scans of small arrays take the small-array tiles
+// plain and segmented add / max / min scans of small arrays take the small-array tiles
 // while the operator's parameters are the library's own.  Host data only
 // (no HIP call).  Called with g_mu held.
 Params choose_params_locked(const Request& r)
@@ -709,8 +723,9 @@ Params choose_params_locked(const Request& r)
     const Params& dflt = g_default_params[r.mode][r.oc];
     const bool library_default = prm.shape == dflt.shape && prm.groups_per_cu == dflt.groups_per_cu &&
                                  prm.handoff == dflt.handoff;
-    if (!r.custom && r.mode == kModePlain && r.oc < kI32ArgMax && library_default) {
-        const int s = small_array_shape(r.n * int64_t(table()[r.mode][r.oc][prm.shape].in_bytes));
+    if (!r.custom && (r.mode == kModePlain || r.mode == kModeSegmented) && r.oc < kI32ArgMax && library_default) {
+        const int64_t bytes = r.n * int64_t(table()[r.mode][r.oc][prm.shape].in_bytes);
+        const int s = (r.mode == kModePlain) ? small_array_shape(bytes) : small_segmented_shape(bytes);
         if (s >= 0) {
             prm.shape = s;
             prm.groups_per_cu = 2;
@@ -842,7 +857,10 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
         a.vec_ok = vec_ok ? 1 : 0;
         a.phase = phase;
         a.store_vec = store_vec ? 1 : 0;
-        if (r.mode == kModeSegmented) {  // the first segment of every block, written before the scan
+        // the first segment of every block, written before the scan (the table's
+        // kernel and the gap before the scan take about 5 us; a workgroup of at most
+        // kSearchedBlocks blocks spends less on searching for its own)
+        if (r.mode == kModeSegmented && M > kSearchedBlocks * B) {
             st = ensure_segment_table(*ws, stream, size_t(M) + 1);
             if (st != LSCAN_OK) return st;
             a.seg_first = ws->seg_first;

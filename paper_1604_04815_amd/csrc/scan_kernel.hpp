@@ -370,21 +370,36 @@ __device__ __forceinline__ typename Op::V chain_prefix(const uint64_t* slot, uin
 typedef const int64_t __attribute__((address_space(4))) CInt64;
 typedef const BatchArray __attribute__((address_space(4))) CBatchArray;
 
-// Up to this many segment heads in a block are matched by a wave-uniform loop;
-// more take a per-lane binary search.
-constexpr int64_t kFewHeads = 32;
-
-// First index k in [lo, hi) with off[k] >= v, or hi.
-__device__ __forceinline__ int64_t lower_bound_i64(const int64_t* off, int64_t lo, int64_t hi, int64_t v)
+// First indices k in [0, S) with off[k] >= v0 (and >= v1), or S, found by one
+// wave: 64 probes a round cut the range by 65, so 2^20 offsets take four
+// rounds.  Offsets that decrease somewhere give some index in [0, S].
+__device__ __forceinline__ void wave_lower_bounds(const int64_t* off, int64_t S, int64_t v0, int64_t v1, int lane,
+                                                  int64_t& k0, int64_t& k1)
 {
-    while (lo < hi) {
-        const int64_t mid = lo + ((hi - lo) >> 1);
-        if (off[mid] < v)
-            lo = mid + 1;
-        else
-            hi = mid;
+    int64_t lo[2] = {0, 0}, hi[2] = {S, S};
+    const int64_t v[2] = {v0, v1};
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+        int64_t x[2], step[2];
+        bool probe[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {  // both probes in flight
+            step[q] = (hi[q] - lo[q] + 64) / 65;  // 1 once at most 65 indices are left
+            const int64_t p = lo[q] + (lane + 1) * step[q] - 1;
+            probe[q] = p < hi[q];
+            x[q] = probe[q] ? off[p] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t below = __popcll(__ballot(probe[q] && x[q] < v[q]));
+            const int64_t first = lo[q] + below * step[q];
+            const int64_t end = first + step[q] - 1;  // the first probe not below, if there is one
+            const bool inside = below < 64 && end < hi[q];
+            lo[q] = first < hi[q] ? first : hi[q];
+            if (inside) hi[q] = end;
+        }
     }
-    return lo;
+    k0 = lo[0];
+    k1 = lo[1];
 }
 
 // Co-residency test run by the host once per (kernel, grid): every
@@ -511,6 +526,11 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     // LDS holds the transpose, stage row by row)
     constexpr bool kStageSpan = kStageY && !kBlocked;
     __shared__ __attribute__((aligned(16))) Out s_ystage[kStageY ? NWAVE : 1][kStageY ? (kStageSpan ? R * ROW : ROW) + E : 1];
+    // segmented scans: one bit per position of a block, set at the segment heads
+    // (clear between blocks: every wave clears its rows' words after reading them)
+    constexpr bool kSeg = MODE == kModeSegmented;
+    constexpr int kHeadWords = R * ROW / 32;  // per wave
+    __shared__ uint32_t s_heads[kSeg ? NWAVE * kHeadWords : 1];
     __shared__ V s_wave_total[2][NWAVE];
     __shared__ VB s_block_prefix[2];
     __shared__ int s_abort[2];
@@ -574,6 +594,11 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
 #pragma unroll
         for (int d = 0; d < kPfOps; ++d) lds_load16(xs + int64_t(d) * (64 * kChunkElems), pf_lds + uint32_t(d) * 1024u);
     };
+
+    if constexpr (kSeg) {
+        for (int w = threadIdx.x; w < NWAVE * kHeadWords; w += T) s_heads[w] = 0;
+        __syncthreads();
+    }
 
     int parity = 0;
     // Batched scans: the array of a block is found by a wave-uniform search
@@ -745,60 +770,37 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             if constexpr (MODE == kModeBatched) {  // while the loads are in flight: the next block's array
                 if (i + B < a.num_blocks) find_array(i + B);
             }
-            if constexpr (MODE == kModeSegmented) {  // segment heads inside this lane's vectors
-                // Found while the data loads are in flight.  The block's range
-                // of offsets comes from the table of first segments per block
-                // that a small kernel writes before the scan (else from two
-                // interleaved wave-uniform binary searches through the scalar
-                // cache); a few heads are then matched against every lane's
-                // vectors, many by a per-lane search.
-                const CInt64* off = (const CInt64*)(a.offsets);
-                const int64_t S = a.num_segments;
+            if constexpr (kSeg) {  // segment heads inside this lane's vectors
+                // The block's range of offsets comes from the table of first segments
+                // per block that a small kernel writes before the scan (two scalar
+                // loads); launches of few blocks search for it.  The workgroup sets the
+                // heads' bits, an offset a lane at a time; then every lane reads the
+                // bits of its vectors.  Bound by the offsets' round trip, once per
+                // block, and the bytes: 25 M int32 in 2^20 segments 53 us (129 us with
+                // a binary search of the offsets per lane and row).
                 int64_t s_lo, s_hi;
-                // offsets count from x, block positions from ph before it
-                if (a.seg_first) {  // the table written just before this launch: two scalar loads
+                if (a.seg_first) {
                     const CInt64* first = (const CInt64*)(a.seg_first);
                     s_lo = first[i];
                     s_hi = first[i + 1];
                 } else {
-                    int64_t lo1 = 0, hi1 = S, lo2 = 0, hi2 = S;
-                    while (lo1 < hi1 || lo2 < hi2) {
-                        const bool a1 = lo1 < hi1, a2 = lo2 < hi2;
-                        const int64_t m1 = a1 ? lo1 + ((hi1 - lo1) >> 1) : 0;
-                        const int64_t m2 = a2 ? lo2 + ((hi2 - lo2) >> 1) : 0;
-                        const int64_t v1 = off[m1], v2 = off[m2];
-                        if (a1) {
-                            if (v1 + ph < tile0) lo1 = m1 + 1; else hi1 = m1;
-                        }
-                        if (a2) {
-                            if (v2 + ph < tile0 + L) lo2 = m2 + 1; else hi2 = m2;
-                        }
-                    }
-                    s_lo = lo1;
-                    s_hi = lo2;
+                    wave_lower_bounds(a.offsets, a.num_segments, tile0 - ph, tile0 - ph + L, lane, s_lo, s_hi);
                 }
-                if (s_hi - s_lo <= kFewHeads) {
-                    for (int64_t k = s_lo; k < s_hi; ++k) {
-                        const int64_t rel = off[k] + ph - lane0;
-#pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            const int64_t d = rel - int64_t(r) * kRowStep;
-                            if (uint64_t(d) < uint64_t(E)) head[r] |= 1u << uint32_t(d);
-                        }
+                if (s_hi > s_lo) {
+                    // offsets count from x, block positions from ph before it
+                    for (int64_t k = s_lo + threadIdx.x; k < s_hi; k += T) {
+                        const uint64_t d = uint64_t(a.offsets[k] + ph - tile0);
+                        if (d < uint64_t(L)) atomicOr(&s_heads[d >> 5], 1u << uint32_t(d & 31));
                     }
-                } else {
+                    __syncthreads();  // lanes read bits that other waves set
+                    uint32_t* heads = &s_heads[wave * kHeadWords];
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        const int64_t p = lane0 + int64_t(r) * kRowStep;
-                        int64_t k = lower_bound_i64(a.offsets, s_lo, s_hi, p - ph);
-                        uint32_t h = 0;
-                        for (; k < s_hi; ++k) {
-                            const int64_t o = a.offsets[k] + ph;
-                            if (o >= p + E) break;
-                            h |= 1u << uint32_t(o - p);
-                        }
-                        head[r] = h;
+                        const int bit = lane * int(kLaneElems) + r * int(kRowStep);
+                        head[r] = (heads[bit >> 5] >> (bit & 31)) & ((1u << E) - 1u);
                     }
+                    wave_lds_sync();  // read before they are cleared
+                    for (int w = lane; w < kHeadWords; w += 64) heads[w] = 0;
                 }
             }
         }
