@@ -15,8 +15,8 @@ struct BatchArray {
     void* y;
     int64_t n;
     int64_t first_block;
-    int64_t phase;    // -1: element path; else x sits this many elements past a vector
-                      // boundary and the array's blocks cover n + phase positions
+    int64_t phase;    // -1: element path; else the array's blocks start this many positions before
+                      // it (a 16-byte boundary of x) and cover n + phase positions
     int64_t stage_y;  // 1: y sits at another phase than x; rows read as vectors are
                       // written through the LDS stage as aligned vectors
 };
@@ -44,8 +44,8 @@ struct ScanArgs {
     uint64_t spin_limit;      // wall-clock ticks one wait may last
     int32_t exclusive;        // 1: exclusive scan
     int32_t vec_ok;           // 1: full blocks read x with full-width vectors
-    int32_t phase;            // plain and segmented scans: x sits this many elements past a vector
-                              // boundary (the block grid is shifted by it; 0 when aligned)
+    int32_t phase;            // plain and segmented scans: the block grid starts this many elements
+                              // before x, on a 16-byte boundary of x
     int32_t store_vec;        // plain and segmented scans: 1 when y sits at the same phase, so full
                               // blocks also write vectors directly (else through an LDS stage, or
                               // element by element for 32-byte output vectors)

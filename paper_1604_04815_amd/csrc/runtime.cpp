@@ -668,36 +668,48 @@ struct Plan {
     int occupancy = 0;
 };
 
-// Where full tiles of x (and y) can use the kernel's vectors: 0 when x sits
-// on a vector boundary and y on 16 bytes; ph > 0 when both sit ph elements
-// past such a boundary (the block grid is then shifted back by ph); -1
-// otherwise (the element-by-element path).
-int64_t alignment_phase(const KernelEntry& k, const void* x, const void* y)
+// Where the block grid of a scan (of each array of a batch) starts: the number
+// of elements before x, fewer than a 128-byte line of outputs holds.  The grid
+// starts on a 16-byte boundary of x (full blocks read vectors); of those
+// positions, one whose outputs start on a line of y, else one whose outputs
+// start on 16 bytes (*store_vec: rows are written straight as vectors), else
+// the last before x (rows are staged).  Rows that start inside a line leave two
+// partial lines per kilobyte (int32 add 2^27, x and y 16 bytes past a line:
+// 180 us, grid on the line 169 us); reads that do cost nothing.  Where the move
+// takes another block, only arrays long enough to gain more than such a block
+// costs (5 us) move the grid to a line.
+constexpr int64_t kLineGridBytes = int64_t(256) << 20;  // of output
+int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n, bool* store_vec)
 {
     const uintptr_t xa = reinterpret_cast<uintptr_t>(x), ya = reinterpret_cast<uintptr_t>(y);
-    const uintptr_t vec_bytes = uintptr_t(k.in_bytes) * uintptr_t(k.elems_per_vec);
-    if (xa % uintptr_t(k.in_bytes) != 0) return -1;
-    const uintptr_t ph = (xa % vec_bytes) / uintptr_t(k.in_bytes);
-    return ya % 16 == (ph * uintptr_t(k.out_bytes)) % 16 ? int64_t(ph) : -1;
+    const int64_t ib = k.in_bytes, ob = k.out_bytes;
+    const int64_t step = std::max<int64_t>(16 / ib, 1), line = std::max<int64_t>(128 / ob, 1);
+    const int64_t first = int64_t(xa % 16) / ib;
+    auto out_offset = [&](int64_t ph, int64_t unit) { return (int64_t(ya % 128) + 128 * ob - ph * ob) % unit; };
+    int64_t vec = -1;  // the first position whose outputs start on 16 bytes
+    for (int64_t ph = first; ph < first + line; ph += step) {
+        if (out_offset(ph, 16) != 0) continue;
+        if (vec < 0) vec = ph;
+        if (out_offset(ph, 128) == 0) {
+            const int64_t L = k.tile_elems;
+            if (n * ob >= kLineGridBytes || (n + ph + L - 1) / L == (n + vec + L - 1) / L) vec = ph;
+            break;
+        }
+    }
+    *store_vec = vec >= 0;
+    return vec >= 0 ? vec : first;
 }
 
-// The path of one array of a batch: x's element phase when x is read with
-// vectors (-1: the element path).  *stage_y is set when y sits at another
-// phase than x, so that rows read as vectors are written through the LDS
-// stage; that needs 16-byte output vectors, else the array takes the element
-// path.
+// The path of one array of a batch: its grid phase when x is read with vectors
+// (-1: the element path).  *stage_y is set when y sits at another phase than
+// the grid, so that rows read as vectors are written through the LDS stage;
+// that needs 16-byte output vectors, else the array takes the element path.
 int64_t batch_phase(const KernelEntry& k, const lscan_array& arr, bool* stage_y)
 {
-    *stage_y = false;
-    const int64_t ph = alignment_phase(k, arr.x, arr.y);
-    if (ph >= 0) return ph;
-    const uintptr_t xa = reinterpret_cast<uintptr_t>(arr.x), ya = reinterpret_cast<uintptr_t>(arr.y);
-    const uintptr_t vec_bytes = uintptr_t(k.in_bytes) * uintptr_t(k.elems_per_vec);
-    if (xa % uintptr_t(k.in_bytes) != 0 || ya % uintptr_t(k.out_bytes) != 0 ||
-        k.out_bytes * k.elems_per_vec != 16)
-        return -1;
-    *stage_y = true;
-    return int64_t((xa % vec_bytes) / uintptr_t(k.in_bytes));
+    bool store_vec = false;
+    const int64_t ph = grid_phase(k, arr.x, arr.y, arr.n, &store_vec);
+    *stage_y = !store_vec && k.out_bytes * k.elems_per_vec == 16;
+    return (store_vec || *stage_y) ? ph : -1;
 }
 
 // Blocks of one array of a batch: its n elements after its alignment phase.
@@ -758,23 +770,17 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
     }
     if (occ <= 0) return LSCAN_ERR_UNSUPPORTED;
 
-    // Plain, segmented and batched scans whose x sits `phase` elements past a vector
-    // boundary, with y at the same element phase, shift the block grid back
-    // by `phase`: the vector accesses of every full tile are then aligned
-    // again, and the blocks cover n + phase positions, the first `phase` of
-    // them empty.
-    // When y sits at another phase than x, the grid follows x: full blocks
-    // still read vectors and write y through an LDS stage.
+    // Plain and segmented scans start their block grid up to a line of outputs
+    // before the array, so that full blocks read whole vectors and write whole
+    // lines: the blocks cover n + phase positions, the first `phase` of them
+    // empty.  When y sits at another phase than x, the grid follows x: full
+    // blocks still read vectors and write y through an LDS stage.
     int32_t phase = 0;
     bool vec_ok = false, store_vec = false;
-    if (r.mode == kModePlain || r.mode == kModeSegmented) {
-        const uintptr_t xa = reinterpret_cast<uintptr_t>(r.x);
-        const uintptr_t vec_bytes = uintptr_t(k.in_bytes) * uintptr_t(k.elems_per_vec);
-        if (xa % uintptr_t(k.in_bytes) == 0) {
-            phase = int32_t((xa % vec_bytes) / uintptr_t(k.in_bytes));
-            vec_ok = true;
-            store_vec = alignment_phase(k, r.x, r.y) >= 0;
-        }
+    if ((r.mode == kModePlain || r.mode == kModeSegmented) &&
+        reinterpret_cast<uintptr_t>(r.x) % uintptr_t(k.in_bytes) == 0) {
+        phase = int32_t(grid_phase(k, r.x, r.y, r.n, &store_vec));
+        vec_ok = true;
     }
 
     const int64_t L = k.tile_elems;
@@ -951,7 +957,8 @@ lscan_status order_after_locked(DeviceOrder* order, hipStream_t stream)
 // ever handed to HIP (kernel arguments, memsets, copies).
 constexpr size_t kNoAllocCtrlWords = 32;               // 256 bytes; the kernels use 7 32-bit words
 constexpr size_t kNoAllocSlotWords = size_t(1) << 19;  // 4 MiB of 64-bit flag words
-static __device__ __align__(256) uint64_t scratch[kNoAllocCtrlWords + kNoAllocSlotWords];
+constexpr size_t kNoAllocSpareWords = 8;  // one more block: a grid shifted by more than one vector
+static __device__ __align__(256) uint64_t scratch[kNoAllocCtrlWords + kNoAllocSlotWords + kNoAllocSpareWords];
 
 constexpr int kMaxNoAllocDevices = 64;
 // The fixed workspace of each device, set up by its first call (scratch
@@ -976,7 +983,7 @@ lscan_status noalloc_workspace_locked(int dev, hipStream_t stream, Workspace** o
         ws.fixed = true;
         ws.ctrl = static_cast<uint32_t*>(ptr);
         ws.slots = static_cast<uint64_t*>(ptr) + kNoAllocCtrlWords;
-        ws.words = kNoAllocSlotWords;
+        ws.words = kNoAllocSlotWords + kNoAllocSpareWords;
         g_noalloc_ready[dev] = true;
     }
     *out = &ws;
@@ -985,8 +992,8 @@ lscan_status noalloc_workspace_locked(int dev, hipStream_t stream, Workspace** o
 
 // Whether the flag words of request r fit the fixed workspace, decided from
 // host data before any device work: M blocks of the kernel r would run
-// (counting the largest alignment shift of the block grid) times its flag
-// words per block.  Called with g_mu held.
+// (counting a shift of the block grid by one vector) times its flag words per
+// block.  Called with g_mu held.
 bool noalloc_fits_locked(const Request& r)
 {
     const Params prm = choose_params_locked(r);

@@ -516,16 +516,17 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     constexpr int64_t kLaneElems = kBlocked ? int64_t(R) * E : E;
     constexpr int64_t kRowStep = kBlocked ? E : ROW;
     __shared__ __attribute__((aligned(16))) u32x4 s_tr[kBlocked ? T * R : 1];
-    // arrays whose y sits at another alignment phase than x: each wave stages
-    // one output row here to write it as aligned vectors
-    constexpr bool kStageY = E * sizeof(Out) == 16;
-    // the rows written as vectors stage the wave's span of them (a wave's rows are
-    // contiguous, and so are the rows of a partial batched block that lie inside
-    // its array) and write it after the last row: one LDS round trip and two
-    // partial vectors per block instead of per row (lane-blocked kernels, whose
-    // LDS holds the transpose, stage row by row)
-    constexpr bool kStageSpan = kStageY && !kBlocked;
-    __shared__ __attribute__((aligned(16))) Out s_ystage[kStageY ? NWAVE : 1][kStageY ? (kStageSpan ? R * ROW : ROW) + E : 1];
+    // arrays whose y sits at another alignment phase than x: each wave stages its
+    // span of the rows written as vectors here (a wave's rows are contiguous, and so
+    // are the rows of a partial block that lie inside its array), at its offset from
+    // the 128-byte line below it, and writes it after the last row: one LDS round
+    // trip per block, and every store instruction writes whole lines (int32 add 2^27,
+    // x one element into its buffer: 187 us staged from 16 bytes, 175 us from the line;
+    // with the outputs moved in registers instead: 187 us).  (Lane-blocked kernels write
+    // from their transpose.)
+    constexpr bool kStageY = E * sizeof(Out) == 16 && !kBlocked;
+    constexpr int kLineOut = 128 / int(sizeof(Out));
+    __shared__ __attribute__((aligned(16))) Out s_ystage[kStageY ? NWAVE : 1][kStageY ? R * ROW + kLineOut : 1];
     // segmented scans: one bit per position of a block, set at the segment heads
     // (clear between blocks: every wave clears its rows' words after reading them)
     constexpr bool kSeg = MODE == kModeSegmented;
@@ -566,11 +567,6 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
 
     // the prefetch: this wave's LDS rows, and whether they hold the block to scan next
     const uint32_t pf_lds = kPrefetch ? lds_address(&s_pf[0]) + uint32_t(wave) * kPfOps * 1024u : 0u;
-    // the 16-byte LDS loads need 16-byte aligned chunks: a grid origin of 8-byte
-    // vectors that is not (bf16 input 8 bytes past a 16-byte boundary) has its
-    // full blocks loaded straight into registers instead
-    const bool pf_ok = kPrefetch && (kVecBytes == 16 ||
-                                     ((reinterpret_cast<uintptr_t>(a.x) - uintptr_t(a.phase) * sizeof(In)) & 15u) == 0);
     bool pf_have = false;
     // the previous step wrote its pending block with at least R vector stores per
     // wave, all issued after the prefetch that the next step waits for
@@ -647,7 +643,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
         } else {
             xg = static_cast<const In*>(a.x) - a.phase;
             t0 = i * L;
-            return pf_ok && a.vec_ok != 0 && t0 + L <= a.n + a.phase && t0 >= a.phase;
+            return a.vec_ok != 0 && t0 + L <= a.n + a.phase && t0 >= a.phase;
         }
     };
     if constexpr (kPrefetch) {
@@ -658,6 +654,18 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             pf_have = true;
         }
     }
+    // Full blocks written at the grid's phase have a fix-up of their own, without
+    // the choice of path per row, in the kernels that their instructions or their
+    // latency bound (4096 segments, int32 add 2^27: 197 -> 192 us; compensated
+    // float32 178 -> 174, int64 max 192 -> 177, bf16 segmented max 223 -> 198).  Long
+    // plain scans at the rate of a copy keep the choice per row: without it they
+    // lose 2.5 % (int32 add 2^28: 334 -> 342 us, however its stores are spaced).
+    // (Short ones gain 3 % by it: 2^20 6.9 -> 6.7 us.)
+    constexpr bool kStraight = MODE != kModePlain || kBlocked || kStage32 ||
+                               (sizeof(V) > 4 && !std::is_same<BaseOp, AddI64>::value);
+    constexpr bool kStraightIfShort = sizeof(V) == 4;
+    const bool straight = kStraight || (kStraightIfShort && a.num_blocks <= 8 * B);
+
     // One pipeline step: load and scan block i (when have_new) while the pending
     // block is resolved and stored.  The step that only drains the last
     // pending block is a separate instantiation, so inside the main loop every
@@ -674,7 +682,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
         int64_t ph = 0;  // alignment phase: the block grid starts ph positions before x
         bool full = false;
         bool svec = true;  // full blocks store vectors (y at the grid's phase)
-        uint32_t vrow = 0;  // batched partial blocks: the wave's rows that lie wholly inside the array
+        uint32_t vrow = 0;  // partial blocks: the wave's rows that lie wholly inside the array
         uint32_t block_head = 0;
         uint32_t head[R];
 #pragma unroll
@@ -695,11 +703,11 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                 block_head = (tile0 == 0) ? 1u : 0u;
                 svec = d.stage_y == 0;
             } else {
-                // arrays that start ph elements past a vector boundary run in
+                // arrays whose block grid starts ph elements before them run in
                 // virtual positions v = index + ph, so that every block but
                 // the first (whose first ph positions hold nothing) is read
-                // and written with whole vectors (plain and segmented scans;
-                // segment offsets move with the grid)
+                // with whole vectors and written with whole lines (plain and
+                // segmented scans; segment offsets move with the grid)
                 ph = a.phase;
                 x = static_cast<const In*>(a.x) - ph;
                 y = static_cast<Out*>(a.y) - ph;
@@ -711,7 +719,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             lane0 = tile0 + int64_t(wave) * (R * ROW) + int64_t(lane) * kLaneElems;
             full = vec_ok && (tile0 + L <= n) && (tile0 >= ph);
             if (full) {
-                if (kPrefetch && pf_ok) {
+                if constexpr (kPrefetch) {
                     // a full block arrives through LDS: prefetched during the previous
                     // step (or, after a partial block, loaded that way now), so no
                     // data load of the compiler's own is ever pending past this point
@@ -747,23 +755,36 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                 } else {
 #pragma unroll
                     for (int r = 0; r < R; ++r) load_vector<In, E>(x + lane0 + int64_t(r) * kRowStep, raw[r]);
-                    // (kernels that prefetch: completed here, off the path of the LDS reads)
-                    if constexpr (kPrefetch) {
-#pragma unroll
-                        for (int r = 0; r < R; ++r) complete_loads(raw[r]);
-                    }
                 }
-            } else if (MODE == kModeBatched && vec_ok) {
-                // an array's first or last block: whole rows of the wave (a
-                // wave-uniform choice) still move as vectors
+            } else {
+                // an array's first or last block, or one that cannot use vectors: whole
+                // rows of the wave (a wave-uniform choice; lane-blocked rows: whole
+                // vectors of the lane) still move as vectors, and every load goes out
+                // before the first wait.  (Element by element with a wait per row, the
+                // one such block of a ragged array took 5 us of its scan.)
                 const int64_t row0 = tile0 + int64_t(wave) * (R * ROW);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int64_t rs = row0 + int64_t(r) * ROW;
-                    if (rs >= ph && rs + ROW <= n) {
-                        load_vector<In, E>(x + lane0 + int64_t(r) * ROW, raw[r]);
-                        vrow |= 1u << r;
+                    if (vec_ok && rs >= ph && rs + ROW <= n) vrow |= 1u << r;
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int64_t p = lane0 + int64_t(r) * kRowStep;
+                    const bool whole = kBlocked ? (vec_ok && p >= ph && p + E <= n) : ((vrow >> r) & 1u) != 0;
+                    if (whole) {
+                        load_vector<In, E>(x + p, raw[r]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < E; ++k) raw[r][k] = (p + k < n && p + k >= ph) ? x[p + k] : In{};
                     }
+                }
+                // prefetching kernels complete these loads here, so that the waits the
+                // compiler places for them never land on the path of full blocks (nor
+                // wait for a prefetch)
+                if constexpr (kPrefetch) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) complete_loads(raw[r]);
                 }
             }
             if constexpr (kPrefetch) pf_have = false;
@@ -867,20 +888,14 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
         // wait of this step on data: vector memory operations complete in issue
         // order, so a later wait on a load of the compiler's own would also wait
         // for the prefetch
-        // (after a partial block, only once its own loads are done: below)
-        bool pf_late = false;
         bool pf_now = false;  // kPfOps prefetch loads per wave issued in this step
         if constexpr (kPrefetch) {
             const In* xg;
             int64_t t0;
             if (have_new && i + B < a.num_blocks && full_src(i + B, xg, t0)) {
-                if (full) {
-                    prefetch(xg, t0);
-                    pf_have = true;
-                    pf_now = true;
-                } else {
-                    pf_late = true;
-                }
+                prefetch(xg, t0);
+                pf_have = true;
+                pf_now = true;
             }
         }
 
@@ -901,56 +916,21 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                         else
                             e[r][k] = lift_elem<BaseOp>(raw[r][k], lane0 + int64_t(r) * kRowStep + k - ph);
                     }
-            } else {
+            } else if constexpr (!kBlocked) {  // (lane-blocked: a zero input word lifts to the identity)
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    // prefetching kernels complete this row's loads here, inside the
-                    // partial-block path, so that the waits the compiler places for
-                    // them never land on the path of full blocks (nor wait for a prefetch)
-                    if constexpr (MODE == kModeBatched) {
-                        if ((vrow >> r) & 1u) {  // a whole row, read as vectors in stage 1
-                            if constexpr (kPrefetch) complete_loads(raw[r]);
-#pragma unroll
-                            for (int k = 0; k < E; ++k)
-                                e[r][k] = lift_elem<BaseOp>(raw[r][k], lane0 + int64_t(r) * ROW + k - ph);
-                            continue;
-                        }
-                    }
-                    In xv[E];
-#pragma unroll
-                    for (int k = 0; k < E; ++k) {
-                        const int64_t p = lane0 + int64_t(r) * kRowStep + k;
-                        xv[k] = (p < n && p >= ph) ? x[p] : In{};
-                    }
-                    if constexpr (kPrefetch) complete_loads(xv);
-                    if constexpr (kBlocked) {  // a zero input word lifts to the identity
-#pragma unroll
-                        for (int k = 0; k < E; ++k) raw[r][k] = xv[k];
-                        continue;
-                    }
+                for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int k = 0; k < E; ++k) {
                         const int64_t p = lane0 + int64_t(r) * kRowStep + k;
                         if (p < n && p >= ph) {
                             if constexpr (MODE == kModeSegmented)
-                                e[r][k] = EOp::make(lift_elem<BaseOp>(xv[k], p - ph), (head[r] >> k) & 1u);
+                                e[r][k] = EOp::make(lift_elem<BaseOp>(raw[r][k], p - ph), (head[r] >> k) & 1u);
                             else
-                                e[r][k] = lift_elem<BaseOp>(xv[k], p - ph);
+                                e[r][k] = lift_elem<BaseOp>(raw[r][k], p - ph);
                         } else {
                             e[r][k] = EOp::identity();
                         }
                     }
-                }
-            }
-            if constexpr (kPrefetch) {
-                if (pf_late) {  // the partial block's loads are done: the next block goes out now
-                    const In* xg;
-                    int64_t t0;
-                    full_src(i + B, xg, t0);
-                    prefetch(xg, t0);
-                    pf_have = true;
-                    pf_now = true;
-                }
             }
             if constexpr (!kBlocked) {
 #pragma unroll
@@ -1035,9 +1015,13 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
         // -- 5. intra-block global scan and one coalesced store per vector, for the pending block:
         //       the block prefix joins each row's lane prefix once, then each element
         //       (inclusive or exclusive is chosen once per block: the flag is uniform,
-        //       and every element's output is then one finish with fixed operands)
-        auto fix_up = [&](auto excl_tag) {
+        //       and every element's output is then one finish with fixed operands;
+        //       and so are, see `straight`, full blocks whose rows are all written as
+        //       vectors at the grid's phase)
+        auto fix_up = [&](auto excl_tag, auto straight_tag) {
             constexpr bool EXCL = decltype(excl_tag)::value;
+            constexpr bool STRAIGHT = decltype(straight_tag)::value;
+            const bool svec = STRAIGHT || p_svec;
             V prefix;
             if constexpr (MODE == kModeBatched)  // the first block of an array starts from the identity
                 prefix = p_block_head ? EOp::identity() : s_block_prefix[parity].v;
@@ -1046,16 +1030,17 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             // lane-blocked rows: the lane's first chunk, and its slot in a striped row
             const int tb = kBlocked ? opaque_lane() * R : 0;
             const int ts = kBlocked ? lds_slot(opaque_lane()) : 0;
-            // staged full blocks: the wave span's offset from the aligned vector below it
+            // staged blocks: the wave span's offset from the line below it
             const int32_t span_shift =
-                kStageSpan ? int32_t((reinterpret_cast<uintptr_t>(p_y + (p_lane0 - int64_t(lane) * E)) % 16) / sizeof(Out))
-                           : 0;
+                kStageY ? int32_t((reinterpret_cast<uintptr_t>(p_y + (p_lane0 - int64_t(lane) * E)) % 128) / sizeof(Out))
+                        : 0;
             // one row of outputs (lane vector r, first position p) to y
             auto store_row = [&](int r, const Out (&out)[E], int64_t p) __attribute__((always_inline)) {
-                // rows read as vectors (a full block, or a whole row of an array's
-                // first or last block) are written as vectors too
-                const bool vec_row = p_full || ((p_vrow >> r) & 1u);
-                if (kStage32 && vec_row && p_svec) {
+                // full blocks are written as vectors, and so are a batch's whole rows of
+                // an array's first or last block (plain and segmented scans have one
+                // such block at either end, whose stores nothing waits for)
+                const bool vec_row = STRAIGHT || p_full || (MODE == kModeBatched && ((p_vrow >> r) & 1u));
+                if (kStage32 && vec_row && svec) {
                     // lane l's 32 bytes are 16-byte chunks 2l and 2l + 1 of the row;
                     // store k writes chunks 64k .. 64k + 63, one per lane.  Chunk c
                     // sits in slot (c & ~7) | ((c + (c >> 3)) & 7): a rotation inside
@@ -1076,38 +1061,12 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                     for (int h = 0; h < 2; ++h)
                         __builtin_nontemporal_store(stage[slot(64 * h + lane)], dst + 64 * h + lane);
                     wave_lds_sync();  // the next row's stage writes come after every lane's reads
-                } else if (vec_row && p_svec) {
+                } else if (vec_row && svec) {
                     store_vector<Out, E>(p_y + p, out);
-                } else if (kStageSpan && vec_row) {  // staged here, written after the last row
+                } else if (kStageY && vec_row) {  // staged here, written after the last row
                     Out* stage = s_ystage[kStageY ? wave : 0];
 #pragma unroll
                     for (int k = 0; k < E; ++k) stage[span_shift + r * ROW + lane * E + k] = out[k];
-                } else if (kStageY && vec_row) {
-                    // y at another phase than the grid: stage the wave's row
-                    // at its offset from the aligned vector below it, then
-                    // write whole aligned vectors (and the partial vectors at
-                    // both ends element by element)
-                    Out* stage = s_ystage[kStageY ? wave : 0];
-                    Out* row_y = p_y + (p - int64_t(lane) * E);  // the wave-row's first output
-                    const int32_t shift = int32_t((reinterpret_cast<uintptr_t>(row_y) % 16) / sizeof(Out));
-#pragma unroll
-                    for (int k = 0; k < E; ++k) stage[shift + lane * E + k] = out[k];
-                    wave_lds_sync();  // lanes read what other lanes wrote
-                    Out* dst = row_y - shift;
-                    const int32_t span = shift + ROW;  // staged outputs occupy [shift, span)
-                    for (int32_t c = lane * E; c < span; c += 64 * E) {
-                        if (c >= shift && c + E <= span) {
-                            Out v[E];
-#pragma unroll
-                            for (int k = 0; k < E; ++k) v[k] = stage[c + k];
-                            store_vector<Out, E>(dst + c, v);
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < E; ++k)
-                                if (c + k >= shift && c + k < span) dst[c + k] = stage[c + k];
-                        }
-                    }
-                    wave_lds_sync();  // the next row's stage writes come after every lane's reads
                 } else {
 #pragma unroll
                     for (int k = 0; k < E; ++k)
@@ -1163,9 +1122,9 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                     store_row(r, out, p_lane0 + int64_t(r) * ROW);
                 }
             }
-            if constexpr (kStageSpan) {
-                const uint32_t vmask = p_full ? ((R == 32) ? ~0u : ((1u << R) - 1u)) : p_vrow;
-                if (!p_svec && vmask != 0) {  // the staged rows: aligned vectors, partial ones at both ends
+            if constexpr (kStageY) {
+                const uint32_t vmask = p_full ? ((R == 32) ? ~0u : ((1u << R) - 1u)) : MODE == kModeBatched ? p_vrow : 0u;
+                if (!svec && vmask != 0) {  // the staged rows: whole vectors, partial ones at both ends
                     wave_lds_sync();  // lanes read what other lanes wrote
                     const Out* stage = s_ystage[kStageY ? wave : 0];
                     Out* dst = p_y + (p_lane0 - int64_t(lane) * E) - span_shift;
@@ -1189,7 +1148,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             }
             if constexpr (kBlocked) {
                 wave_lds_sync();  // lanes read what other lanes wrote
-                if (p_full && !p_svec) {
+                if (p_full && !svec) {
                     // y at another phase than the grid: aligned output vector k holds the
                     // wave's outputs k*E - shift .. k*E - shift + E - 1, taken from
                     // staged chunks k - 1 and k (the partial vectors at both ends of the
@@ -1244,14 +1203,20 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             }
         };
         if (have_pend) {
-            if (a.exclusive)
-                fix_up(std::true_type{});
+            auto by_form = [&](auto straight_tag) __attribute__((always_inline)) {
+                if (a.exclusive)
+                    fix_up(std::true_type{}, straight_tag);
+                else
+                    fix_up(std::false_type{}, straight_tag);
+            };
+            if ((kStraight || kStraightIfShort) && p_full && p_svec && straight)
+                by_form(std::bool_constant<kStraight || kStraightIfShort>{});
             else
-                fix_up(std::false_type{});
+                by_form(std::false_type{});
         }
-        // full blocks with y at the grid's phase leave through one vector store per
-        // row (two for 32-byte lane outputs), after any prefetch of this step
-        pf_then_stores = have_pend && p_full && p_svec;
+        // full blocks leave through at least one store instruction per row, after any
+        // prefetch of this step
+        pf_then_stores = have_pend && p_full;
         // the window of the new block, for the next step's fold
         if (kPrefetch && wave == 0) {
             flags_have = false;

@@ -294,3 +294,28 @@ def test_small_arrays_take_small_tiles(gpu_lib):
             d = gpu_lib.lscan_get_params(gpu_lib.I32, gpu_lib.ADD)
             assert info.block_threads == d.block_threads, (n, info.block_threads)
         compare(to_host(y), x, "int32", "add", False, what=f"small-array shapes n={n}")
+
+
+@pytest.mark.parametrize("dtype,op", [("int32", "add"), ("int64", "max"), ("float32", "max"), ("bfloat16", "max")])
+def test_block_grid_starts_on_a_line_of_y(gpu_lib, dtype, op):
+    # x and y at 16-byte steps of a 128-byte line (and off them), so that the grid
+    # starts up to a line before the array; sizes whose first and last blocks hold
+    # whole rows, single rows, and rows cut at either end
+    in_bytes = {"int32": 4, "int64": 8, "float32": 4, "bfloat16": 2}[dtype]
+    step = 16 // in_bytes
+    x0 = make_input(dtype, op, 70_000, seed=31)
+    for n in (1, 63, 4095, 4097, 16_384, 65_536 + 129):
+        for xo, yo in ((0, 0), (step, step), (3 * step, 3 * step), (0, 16), (step, 8), (1, 1), (1, 0), (step + 1, 5)):
+            log(f"[parity] line grid {dtype}/{op} n={n} x+{xo} y+{yo}")
+            x = x0[:n]
+            xd = to_device(x, dtype)
+            buf = torch.zeros(n + 64, dtype=xd.dtype, device="cuda")
+            buf[xo:xo + n] = xd
+            out = torch.empty(n + 64, dtype=gpu_lib.out_dtype(buf, op), device="cuda")
+            for excl in (False, True):
+                call = gpu_lib.exclusive if excl else gpu_lib.inclusive
+                out.fill_(7)
+                call(buf[xo:xo + n], op, out=out[yo:yo + n])
+                what = f"line grid {dtype}/{op} n={n} x+{xo} y+{yo} excl={excl}"
+                compare(to_host(out[yo:yo + n]), x, dtype, op, excl, what=what)
+                assert bool((out[:yo] == 7).all()) and bool((out[yo + n:] == 7).all()), f"{what}: writes outside y"

@@ -137,3 +137,25 @@ def test_segmented_unaligned(gpu_lib, dtype, op, comp):
                     what=f"seg unaligned {dtype}/{op} x+{xo} y+{yo} excl={excl}")
         # nothing written outside y
         assert torch.all(yb[:yo] == 7).item() and torch.all(yb[yo + n:] == 7).item()
+
+
+@pytest.mark.parametrize("table", [False, True], ids=["searched", "table"])
+@pytest.mark.parametrize("segments", [1, 64, 65, 66, 4160, 4161, 90_000])
+def test_segment_ranges(gpu_lib, segments, table):
+    # launches of few blocks search the offsets, 64 probes a round; longer ones read
+    # a table of first segments: segment counts around whole rounds, both ways, with
+    # runs of empty segments and blocks with more heads than threads
+    n = 700_001 if not table else 3_000_001
+    g = np.random.default_rng(segments)
+    cuts = np.sort(g.choice(n // 3, segments - 1)) if segments > 1 else np.zeros(0, np.int64)
+    off = np.concatenate([[0], cuts, [n]]).astype(np.int64)
+    params = gpu_lib.Params(256, 2, 1, 0) if table else None   # 2048-element blocks: over two per workgroup
+    for dtype, op in (("int32", "add"), ("float32", "max")):
+        x = make_input(dtype, op, n, seed=segments)
+        log(f"[seg] ranges S={segments} table={table} {dtype}/{op}")
+        for excl in (False, True):
+            y = gpu_lib.segmented(to_device(x, dtype), torch.from_numpy(off).to("cuda"), op, exclusive=excl, params=params)
+            gpu_lib.lscan_check(torch.cuda.current_stream().cuda_stream)
+            info = gpu_lib.lscan_last_launch()
+            assert (info.num_blocks > 2 * info.grid) == table
+            compare(to_host(y), x, dtype, op, excl, offsets=off, what=f"S={segments} table={table} {dtype}/{op}/{excl}")
