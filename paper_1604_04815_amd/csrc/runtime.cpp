@@ -166,6 +166,16 @@ int small_segmented_shape(int64_t bytes)
     return -1;
 }
 
+// And for running argmax / argmin with 32-bit indices (float32 keys: 2^14 6.3
+// against 10.2 us at 512 x 8, 2^19 7.5 / 10.8, 2^21 10.5 / 13.1; from 2^22 on
+// 512 x 8 is the best shape).
+int small_arg_shape(int64_t bytes)
+{
+    if (bytes <= (int64_t(2) << 20)) return 6;  // 512 x 2
+    if (bytes <= (int64_t(8) << 20)) return 5;  // 1024 x 2
+    return -1;
+}
+
 // Segmented launches of at most this many blocks per workgroup search the
 // offsets for each block instead of reading the table of first segments.
 constexpr int64_t kSearchedBlocks = 2;
@@ -217,9 +227,8 @@ void init_params_locked()
     for (int o = kI32ArgMax; o <= kF32ArgMin; ++o) g_params[kModePlain][o] = t1024x2;
     // the 32-bit-index argmax / argmin kernels prefetch too (int32 keys, 2^28:
     // 256 x 8 two per CU 773 us, 512 x 8 one per CU 677 us)
+    // (int64 keys, 2^25: 1024 x 4 134 us, 512 x 8 131 us)
     for (int o = kI32ArgMaxS; o <= kF32ArgMinS; ++o) g_params[kModePlain][o] = t512x8g1;
-    g_params[kModePlain][kI64ArgMaxS] = t1024x4;
-    g_params[kModePlain][kI64ArgMinS] = t1024x4;
     for (int o = 0; o < kNumOpCodes; ++o) {
         // with the per-block segment table and (sums) lane-blocked rows; 512 x 8
         // (4096 segments, int32 add: 5.81 TB/s), whose kernels keep their
@@ -725,7 +734,7 @@ int64_t batch_blocks(const KernelEntry& k, const lscan_array& arr, int64_t L)
 // arguments.  Called with g_mu held.  ws_fixed is a workspace owned by a
 // graph, or null for the per-stream one.
 // The parameters a request runs with: the caller's, else the operator's;
-// plain and segmented add / max / min scans of small arrays take the small-array tiles
+// scans of small arrays take the small-array tiles
 // while the operator's parameters are the library's own.  Host data only
 // (no HIP call).  Called with g_mu held.
 Params choose_params_locked(const Request& r)
@@ -735,9 +744,13 @@ Params choose_params_locked(const Request& r)
     const Params& dflt = g_default_params[r.mode][r.oc];
     const bool library_default = prm.shape == dflt.shape && prm.groups_per_cu == dflt.groups_per_cu &&
                                  prm.handoff == dflt.handoff;
-    if (!r.custom && (r.mode == kModePlain || r.mode == kModeSegmented) && r.oc < kI32ArgMax && library_default) {
+    const bool small_kind = (r.mode == kModePlain && (r.oc < kI32ArgMax || r.oc >= kI32ArgMaxS)) ||
+                            r.mode == kModeSegmented;
+    if (!r.custom && small_kind && library_default) {
         const int64_t bytes = r.n * int64_t(table()[r.mode][r.oc][prm.shape].in_bytes);
-        const int s = (r.mode == kModePlain) ? small_array_shape(bytes) : small_segmented_shape(bytes);
+        const int s = r.mode == kModeSegmented ? small_segmented_shape(bytes)
+                      : r.oc >= kI32ArgMaxS    ? small_arg_shape(bytes)
+                                               : small_array_shape(bytes);
         if (s >= 0) {
             prm.shape = s;
             prm.groups_per_cu = 2;

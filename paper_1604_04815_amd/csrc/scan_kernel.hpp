@@ -664,7 +664,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     constexpr bool kStraight = MODE != kModePlain || kBlocked || kStage32 ||
                                (sizeof(V) > 4 && !std::is_same<BaseOp, AddI64>::value);
     constexpr bool kStraightIfShort = sizeof(V) == 4;
-    const bool straight = kStraight || (kStraightIfShort && a.num_blocks <= 8 * B);
+    const bool straight = kStraight || (kStraightIfShort && a.num_blocks <= 2 * B);
 
     // One pipeline step: load and scan block i (when have_new) while the pending
     // block is resolved and stored.  The step that only drains the last
@@ -771,12 +771,17 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int64_t p = lane0 + int64_t(r) * kRowStep;
+                    const int64_t rs = row0 + int64_t(r) * ROW;
                     const bool whole = kBlocked ? (vec_ok && p >= ph && p + E <= n) : ((vrow >> r) & 1u) != 0;
+                    const bool none = kBlocked ? (p >= n || p + E <= ph) : (rs >= n || rs + ROW <= ph);
+#pragma unroll
+                    for (int k = 0; k < E; ++k) raw[r][k] = In{};
                     if (whole) {
                         load_vector<In, E>(x + p, raw[r]);
-                    } else {
+                    } else if (!none) {
 #pragma unroll
-                        for (int k = 0; k < E; ++k) raw[r][k] = (p + k < n && p + k >= ph) ? x[p + k] : In{};
+                        for (int k = 0; k < E; ++k)
+                            if (p + k < n && p + k >= ph) raw[r][k] = x[p + k];
                     }
                 }
                 // prefetching kernels complete these loads here, so that the waits the
