@@ -5,9 +5,10 @@
  *
  * Flag epochs (paper, Section 4.3 and Algorithm 4; the paper does not say
  * how its flag array is reset between scans).  Every launch tags the flag
- * words it writes with a 32-bit epoch: the kernel reads the last tag from a
- * control word, uses tag + 1, and the last workgroup to leave stores it
- * back, so no memset is needed between launches.  Before the tag could wrap
+ * words it writes with a 32-bit epoch, one more than the launch before on its
+ * workspace, so no memset is needed between launches: the host counts the tags
+ * of eager launches; a graph replay reads the last tag from a control word,
+ * and its last workgroup to leave stores the new one back.  Before the tag could wrap
  * (after lscan_test_epoch_limit() launches on one workspace) the library
  * starts a new epoch run: it clears every flag word, restarts the tag and
  * the exit counter, and clears the word that holds the tag of the last
@@ -17,7 +18,7 @@
  *
  * Control words of a workspace, as returned in ctrl[4]:
  *   ctrl[0]  tag of the last completed launch
- *   ctrl[1]  exit counter of the running launch (0 between launches)
+ *   ctrl[1]  exit counter of the running graph replay (0 between launches)
  *   ctrl[2]  timeout flag (set by a launch that gave up; cleared by
  *            lscan_check / lscan_graph_check)
  *   ctrl[3]  tag of the last launch that gave up (0: none since the last

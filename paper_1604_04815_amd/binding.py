@@ -14,6 +14,8 @@ from __future__ import annotations
 import ctypes
 import os
 
+import torch
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG, "liblscan.so")
 
@@ -141,8 +143,6 @@ def load(path: str | None = None):
     global _lib
     if _lib is not None and path is None:
         return _lib
-    import torch  # noqa: F401  -- share torch's HIP runtime
-
     p = path or LIB_PATH
     if not os.path.exists(p):
         raise RuntimeError(f"{p} is not built: run __graft_entry__.build() "
@@ -366,30 +366,33 @@ def lscan_test_epoch_state(stream=None, graph: Graph | None = None):
 # torch tensor marshalling
 # ---------------------------------------------------------------------------
 
-def dtype_code(t) -> int:
-    import torch
+# These run once per call, and a scan of a few thousand elements takes the
+# device 4 us: they look at each tensor once and build no objects.
+_DTYPE_CODES = {torch.int32: I32, torch.int64: I64, torch.float32: F32, torch.bfloat16: BF16}
 
-    table = {torch.int32: I32, torch.int64: I64, torch.float32: F32, torch.bfloat16: BF16}
-    if t.dtype not in table:
+
+def dtype_code(t) -> int:
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
         raise TypeError(f"unsupported dtype {t.dtype}")
-    return table[t.dtype]
+    return code
 
 
 def out_dtype(t, op="add"):
-    import torch
-
-    if op in ("argmax", "argmin"):
+    if op == "argmax" or op == "argmin":
         return torch.int64  # indices
-    return torch.float32 if t.dtype == torch.bfloat16 else t.dtype
+    dtype = t.dtype
+    return torch.float32 if dtype is torch.bfloat16 else dtype
+
+
+# the current stream's raw handle without building a Stream object, where torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream) -> int:
-    import torch
-
     if stream is None:
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None:  # the raw handle without building a Stream object (a few microseconds less)
-            return raw(torch.cuda.current_device())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -403,12 +406,10 @@ def _flat(t, name):
 
 
 def _out_for(x, out, op="add"):
-    import torch
-
     if out is None:
         return torch.empty(x.shape[0], dtype=out_dtype(x, op), device=x.device)
     _flat(out, "out")
-    if out.dtype != out_dtype(x, op) or out.shape[0] != x.shape[0]:
+    if out.dtype != out_dtype(x, op) or out.numel() != x.numel():
         raise ValueError("out has the wrong dtype or length")
     return out
 
@@ -421,7 +422,7 @@ def inclusive(x, op="add", compensated=False, out=None, stream=None, params: Par
     y = _out_for(x, out, op)
     flags = (F_COMPENSATED if compensated else 0) | (F_INDEX64 if index64 else 0)
     if params is None:
-        lscan_inclusive(x.data_ptr(), y.data_ptr(), x.shape[0], dtype_code(x), OPS[op], flags, _stream(stream))
+        lscan_inclusive(x.data_ptr(), y.data_ptr(), x.numel(), dtype_code(x), OPS[op], flags, _stream(stream))
     else:
         lscan_scan_with_params(x.data_ptr(), y.data_ptr(), x.shape[0], dtype_code(x), OPS[op], flags, 0,
                                params, _stream(stream))
@@ -435,7 +436,7 @@ def exclusive(x, op="add", compensated=False, out=None, stream=None, params: Par
     y = _out_for(x, out, op)
     flags = (F_COMPENSATED if compensated else 0) | (F_INDEX64 if index64 else 0)
     if params is None:
-        lscan_exclusive(x.data_ptr(), y.data_ptr(), x.shape[0], dtype_code(x), OPS[op], flags, _stream(stream))
+        lscan_exclusive(x.data_ptr(), y.data_ptr(), x.numel(), dtype_code(x), OPS[op], flags, _stream(stream))
     else:
         lscan_scan_with_params(x.data_ptr(), y.data_ptr(), x.shape[0], dtype_code(x), OPS[op], flags, 1,
                                params, _stream(stream))
@@ -445,8 +446,6 @@ def exclusive(x, op="add", compensated=False, out=None, stream=None, params: Par
 def segmented(x, offsets, op="add", exclusive=False, compensated=False, out=None, stream=None,
               params: Params | None = None):
     """Scan of every segment x[off[s]:off[s+1]] in one launch; returns y."""
-    import torch
-
     _flat(x, "x")
     _flat(offsets, "offsets")
     if offsets.dtype != torch.int64:
@@ -491,8 +490,6 @@ def compact(x, keep=None, out=None, count=None, stream=None, params: Params | No
     has room for every item and holds the kept ones in ``out[:count]``;
     ``count`` is a one-element int64 device tensor (read it after the stream
     has synchronized)."""
-    import torch
-
     _flat(x, "x")
     n = x.shape[0]
     if keep is not None:
@@ -518,8 +515,6 @@ def radix_offsets(keys, shift, bits, block_items, out=None, stream=None):
     """Digit offsets of one radix-sort pass over the device tensor ``keys``
     (int32 / float32 / int64, read as unsigned bit patterns): an int64 device
     tensor of shape (2**bits, M), M = ceil(n / block_items)."""
-    import torch
-
     _flat(keys, "keys")
     n = keys.shape[0]
     m = (n + block_items - 1) // block_items if n else 0
@@ -539,8 +534,6 @@ def scan_custom(kernel, x, n, out=None, exclusive=False, stream=None, params: Pa
     tensor ``x`` with the kernel handle ``kernel`` (made in the user's own
     library with include/lscan_custom.hpp); ``out`` (default: a tensor like
     ``x``) receives n elements of its Out type.  Returns ``out``."""
-    import torch
-
     _flat(x, "x")
     if out is None:
         out = torch.empty_like(x)
@@ -583,8 +576,6 @@ def bfs(row_offsets, cols, source, levels=None, parents=True, stats=None, stream
     int32 levels (-1 unreached); int32 parents of a breadth-first tree, or
     None when ``parents`` is False; an int64 device tensor of 4 (levels,
     vertices reached, edges scanned, malformed entries)."""
-    import torch
-
     _flat(row_offsets, "row_offsets")
     _flat(cols, "cols")
     if row_offsets.dtype != torch.int64 or cols.dtype != torch.int32:

@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int64_t B = gridDim.x;
-    const uint32_t tag = __hip_atomic_load(a.ctrl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    const uint32_t tag = launch_tag(a);
     const T* x = static_cast<const T*>(a.x);
     T* out = static_cast<T*>(a.y);
     const uint8_t* keep = a.keep;
@@ -382,14 +382,7 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
     if (live && have_pend) step(std::false_type{}, i);
     if constexpr (kPrefetch) vmem_drain();  // no LDS load outlives the workgroup
 
-    // count out; the last workgroup advances the epoch (as in the scan)
-    if (threadIdx.x == 0) {
-        const uint32_t prev = __hip_atomic_fetch_add(a.ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev == uint32_t(gridDim.x) - 1u) {
-            __hip_atomic_store(a.ctrl + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(a.ctrl, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    leave_launch(a, tag);
 }
 
 template <class T, int TT, int R>

@@ -38,7 +38,7 @@ struct ScanArgs {
     const BatchArray* arrays; // batched: num_arrays + 1 descriptors (device), else null
     int64_t num_arrays;
     uint64_t* slots;          // M * slot_words flag words (epoch tag | data)
-    uint32_t* ctrl;           // [0] last epoch tag, [1] exit counter, [2] timeout flag,
+    uint32_t* ctrl;           // [0] last epoch tag and [1] exit counter of graph replays, [2] timeout flag,
                               // [3] tag of the last launch that gave up a wait,
                               // [4] residency arrivals, [5] residency failure, [6] residency exits
     uint64_t spin_limit;      // wall-clock ticks one wait may last
@@ -54,6 +54,8 @@ struct ScanArgs {
     uint32_t* status_host;    // optional host-visible word that also receives the timeout flag
     const uint8_t* keep;      // compaction: one keep byte per item (null: keep non-zero items)
     int64_t* count;           // compaction: receives the number of kept items (device)
+    uint32_t tag;             // the launch's epoch tag, or 0: last tag + 1, read from ctrl and stored back
+                              // by the last workgroup to leave (graph replays, whose arguments are fixed)
     const int64_t* seg_first; // segmented: M + 1 entries, the first segment whose offset is at
                               // or past block i's start (null: the kernel searches the offsets)
 };
@@ -69,7 +71,7 @@ hipError_t launch_segment_table(const ScanArgs& a, int64_t tile_elems, hipStream
 // the same layout as the runtime.  High half: a fixed mark; then the size
 // of ScanArgs; low nibble: a revision for same-size layout changes.
 constexpr uint32_t kKernelAbiMark = 0x4C530000u;
-constexpr uint32_t kKernelAbi = kKernelAbiMark | (uint32_t(sizeof(ScanArgs)) << 4) | 3u;
+constexpr uint32_t kKernelAbi = kKernelAbiMark | (uint32_t(sizeof(ScanArgs)) << 4) | 4u;
 static_assert(sizeof(ScanArgs) < 4096, "the size of ScanArgs fits the tag");
 
 struct KernelEntry {

@@ -100,8 +100,9 @@ struct DeviceInfo {
 struct Workspace {
     uint64_t* slots = nullptr;
     size_t words = 0;
-    uint32_t* ctrl = nullptr;   // [0] last tag, [1] exit counter, [2] timeout flag, [4..6] residency test
+    uint32_t* ctrl = nullptr;   // [0] last tag, [1] exit counter (of graph replays), [2] timeout flag, [4..6] residency test
     uint64_t launches = 0;
+    uint32_t tag = 0;           // of the last launch (a graph's workspace counts its tags on the device)
     BatchArray* desc = nullptr;        // device copy of the descriptor table
     size_t desc_cap = 0;
     BatchArray* desc_host = nullptr;   // pinned staging copy
@@ -519,6 +520,7 @@ lscan_status reset_epoch(Workspace& ws, hipStream_t stream)
     if (e == hipSuccess && ws.ctrl) e = hipMemsetAsync(ws.ctrl + 3, 0, sizeof(uint32_t), stream);
     if (e != hipSuccess) return device_error(e);
     ws.launches = 0;
+    ws.tag = 0;
     return LSCAN_OK;
 }
 
@@ -1044,9 +1046,11 @@ lscan_status run(const Request& r, void* stream_ptr)
         e = launch_segment_table(plan.a, plan.k->tile_elems, stream);
         if (e != hipSuccess) return device_error(e);
     }
+    plan.a.tag = ws->tag + 1;
     e = plan.k->launch(plan.a, plan.grid, stream);
     if (e != hipSuccess) return device_error(e);
     ws->launches++;
+    ws->tag++;
     return order_after_locked(order, stream);
 }
 
@@ -1072,9 +1076,11 @@ lscan_status run_noalloc(const Request& r, void* stream_ptr)
     Plan plan;
     st = plan_locked(r, dev, ws, stream, &plan, nullptr);
     if (st != LSCAN_OK) return st;
+    plan.a.tag = ws->tag + 1;
     e = plan.k->launch(plan.a, plan.grid, stream);
     if (e != hipSuccess) return device_error(e);
     ws->launches++;
+    ws->tag++;
     return LSCAN_OK;
 }
 
@@ -1557,15 +1563,18 @@ lscan_status seed_epoch(Workspace& ws, uint64_t launches, uint32_t tag, uint32_t
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) return device_error(e);
     ws.launches = launches;
+    ws.tag = tag;
     return LSCAN_OK;
 }
 
-lscan_status epoch_state(const Workspace& ws, uint64_t* launches, uint32_t* ctrl)
+// device_tag: a graph's workspace, whose tags are counted on the device.
+lscan_status epoch_state(const Workspace& ws, bool device_tag, uint64_t* launches, uint32_t* ctrl)
 {
     if (!launches || !ctrl) return LSCAN_ERR_INVALID_ARG;
     if (!ws.ctrl) return LSCAN_ERR_NOT_FOUND;
     const hipError_t e = hipMemcpy(ctrl, ws.ctrl, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return device_error(e);
+    if (!device_tag) ctrl[0] = ws.tag;
     *launches = ws.launches;
     return LSCAN_OK;
 }
@@ -1613,7 +1622,7 @@ lscan_status lscan_test_epoch_state(void* stream, uint64_t* launches, uint32_t c
     Workspace* ws = nullptr;
     lscan_status st = stream_workspace_synced(stream, &ws);
     if (st != LSCAN_OK) return st;
-    return ws ? epoch_state(*ws, launches, ctrl) : LSCAN_ERR_NOT_FOUND;
+    return ws ? epoch_state(*ws, false, launches, ctrl) : LSCAN_ERR_NOT_FOUND;
 }
 
 lscan_status lscan_test_graph_epoch_state(lscan_graph* g, uint64_t* launches, uint32_t ctrl[4])
@@ -1621,7 +1630,7 @@ lscan_status lscan_test_graph_epoch_state(lscan_graph* g, uint64_t* launches, ui
     if (!g) return LSCAN_ERR_INVALID_ARG;
     const hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return device_error(e);
-    return epoch_state(g->ws, launches, ctrl);
+    return epoch_state(g->ws, true, launches, ctrl);
 }
 
 int32_t lscan_num_tile_shapes(void) { return kNumShapes; }

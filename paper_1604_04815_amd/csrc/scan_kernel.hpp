@@ -402,6 +402,26 @@ __device__ __forceinline__ void wave_lower_bounds(const int64_t* off, int64_t S,
     k1 = lo[1];
 }
 
+// The launch's epoch tag.  The host counts the launches on a workspace and hands
+// each its tag; a graph's replays share their arguments, so they take the tag
+// after the one in the workspace, and the last workgroup to leave stores it
+// back (no memset needed between launches).  Counting workgroups out costs the
+// tail of every launch an atomic on one word per workgroup.
+__device__ __forceinline__ uint32_t launch_tag(const ScanArgs& a)
+{
+    return a.tag ? a.tag : __hip_atomic_load(a.ctrl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+}
+__device__ __forceinline__ void leave_launch(const ScanArgs& a, uint32_t tag)
+{
+    if (a.tag == 0 && threadIdx.x == 0) {
+        const uint32_t prev = __hip_atomic_fetch_add(a.ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (prev == uint32_t(gridDim.x) - 1u) {
+            __hip_atomic_store(a.ctrl + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.ctrl, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 // Co-residency test run by the host once per (kernel, grid): every
 // workgroup counts itself in and waits, for at most `limit` ticks, until all
 // gridDim.x have arrived.  Any workgroup that stops waiting before that sets
@@ -539,7 +559,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int64_t B = gridDim.x;
-    const uint32_t tag = __hip_atomic_load(a.ctrl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+    const uint32_t tag = launch_tag(a);
 
     // The block scanned in the previous iteration waits, in registers, for
     // its prefix: it is resolved (window fold) and stored one iteration
@@ -757,31 +777,29 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                     for (int r = 0; r < R; ++r) load_vector<In, E>(x + lane0 + int64_t(r) * kRowStep, raw[r]);
                 }
             } else {
-                // an array's first or last block, or one that cannot use vectors: whole
-                // rows of the wave (a wave-uniform choice; lane-blocked rows: whole
-                // vectors of the lane) still move as vectors, and every load goes out
-                // before the first wait.  (Element by element with a wait per row, the
-                // one such block of a ragged array took 5 us of its scan.)
+                // an array's first or last block, or one that cannot use vectors: in
+                // batches, where such blocks are many, whole rows of the wave (a
+                // wave-uniform choice) still move as vectors; the others element by
+                // element, from positions held inside the array, so that no load hangs
+                // on a condition and all go out before the first wait.  (With a wait
+                // per row, the one such block of a ragged array took 5 us of its scan.)
                 const int64_t row0 = tile0 + int64_t(wave) * (R * ROW);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int64_t rs = row0 + int64_t(r) * ROW;
-                    if (vec_ok && rs >= ph && rs + ROW <= n) vrow |= 1u << r;
+                    if (MODE == kModeBatched && vec_ok && rs >= ph && rs + ROW <= n) vrow |= 1u << r;
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int64_t p = lane0 + int64_t(r) * kRowStep;
-                    const int64_t rs = row0 + int64_t(r) * ROW;
-                    const bool whole = kBlocked ? (vec_ok && p >= ph && p + E <= n) : ((vrow >> r) & 1u) != 0;
-                    const bool none = kBlocked ? (p >= n || p + E <= ph) : (rs >= n || rs + ROW <= ph);
+                    const int64_t p0 = lane0 + int64_t(r) * kRowStep;
+                    if (MODE == kModeBatched && ((vrow >> r) & 1u)) {
+                        load_vector<In, E>(x + p0, raw[r]);
+                    } else {
 #pragma unroll
-                    for (int k = 0; k < E; ++k) raw[r][k] = In{};
-                    if (whole) {
-                        load_vector<In, E>(x + p, raw[r]);
-                    } else if (!none) {
-#pragma unroll
-                        for (int k = 0; k < E; ++k)
-                            if (p + k < n && p + k >= ph) raw[r][k] = x[p + k];
+                        for (int k = 0; k < E; ++k) {
+                            const int64_t p = p0 + k;
+                            raw[r][k] = x[p < ph ? ph : p < n ? p : n - 1];
+                        }
                     }
                 }
                 // prefetching kernels complete these loads here, so that the waits the
@@ -790,6 +808,15 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                 if constexpr (kPrefetch) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) complete_loads(raw[r]);
+                }
+                if constexpr (kBlocked) {  // a zero input word lifts to the identity
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int k = 0; k < E; ++k) {
+                            const int64_t p = lane0 + int64_t(r) * kRowStep + k;
+                            if (p < ph || p >= n) raw[r][k] = In{};
+                        }
                 }
             }
             if constexpr (kPrefetch) pf_have = false;
@@ -921,7 +948,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                         else
                             e[r][k] = lift_elem<BaseOp>(raw[r][k], lane0 + int64_t(r) * kRowStep + k - ph);
                     }
-            } else if constexpr (!kBlocked) {  // (lane-blocked: a zero input word lifts to the identity)
+            } else if constexpr (!kBlocked) {
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -1281,15 +1308,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     if (live && have_pend) step(std::false_type{}, i);
     vmem_drain();  // no load into LDS outlives the workgroup
 
-    // Every workgroup counts itself out; the last one advances the epoch so
-    // the next launch on this workspace uses a fresh tag (no memset needed).
-    if (threadIdx.x == 0) {
-        const uint32_t prev = __hip_atomic_fetch_add(a.ctrl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (prev == uint32_t(gridDim.x) - 1u) {
-            __hip_atomic_store(a.ctrl + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(a.ctrl, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    leave_launch(a, tag);
 }
 
 // ---------------------------------------------------------------------------
