@@ -19,10 +19,10 @@
 //     own previous P(i - B) and the B - 1 counts in between (the window
 //     hand-off of the scan), so the count carried between blocks is 64-bit;
 //   * the pending block then writes each kept element to its position; the
-//     kept elements of a wave-row land in one contiguous range of out, so
-//     each wave stages the row in LDS at its offsets from the aligned vector
-//     below the range and writes it as whole aligned 16-byte vectors (items
-//     one by one only in the partial vectors at both ends).
+//     kept elements of a wave's rows land in one contiguous range of out, so
+//     each wave stages them in LDS at their offsets from the 128-byte line
+//     below the range and writes whole aligned 16-byte vectors (items one by
+//     one only in the partial vectors at both ends).
 // The workgroup that resolves the last block writes the total count.
 #pragma once
 
@@ -90,9 +90,10 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
     __shared__ int32_t s_wave_total[2][NWAVE];
     __shared__ VB s_block_prefix[2];
     __shared__ int s_abort[2];
-    // per wave: one row of kept items, laid out as in out (shifted by the
-    // row's misalignment), so that it leaves in aligned 16-byte vectors
-    __shared__ __attribute__((aligned(16))) T s_stage[NWAVE][ROW + E];
+    // per wave: the kept items of its rows, laid out as in out from a 128-byte line
+    // on, so that every store instruction writes whole lines
+    constexpr int kLine = 128 / int(sizeof(T));
+    __shared__ __attribute__((aligned(16))) T s_stage[NWAVE][R * ROW + kLine];
     // per wave: the keep bytes of its R rows, as read from memory
     __shared__ __attribute__((aligned(16))) uint8_t s_flags[NWAVE][R * ROW];
     using FC = FlagChunks<R, E>;
@@ -115,8 +116,7 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
     uint32_t p_bits[R];
     int32_t p_row0[R];
     int32_t p_lane[R];
-    int32_t p_rowcnt[R];
-    const bool out_vec = (reinterpret_cast<uintptr_t>(out) % 16) == 0;
+    int32_t p_total = 0;  // kept items of the wave's rows
     VB p_agg = 0;    // wave 0: kept items in the pending block
     VB carry = 0;    // wave 0: kept items before block (pending - B + 1)
 
@@ -130,6 +130,9 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
     const uint32_t pfx_lds = kPrefetch ? lds_address(&s_pfx[0]) + uint32_t(wave) * R * 1024u : 0u;
     const uint32_t pff_lds = kPrefetch ? lds_address(&s_flags[wave][0]) : 0u;
     bool pf_have = false;
+    // the store instructions of whole vectors that the previous step issued, all
+    // after the prefetch that the next step waits for (a lower bound of its stores)
+    int pf_then_stores = 0;
     auto full_block = [&](int64_t i) -> bool { return a.vec_ok && ((i + 1) * L <= n); };
     auto prefetch = [&](int64_t i) {
         const int64_t w0 = i * L + int64_t(wave) * (R * ROW);
@@ -165,7 +168,12 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
             // step, or loaded that way now after a partial block)
             if (have_new && full) {
                 if (!pf_have) prefetch(i);
-                vmem_drain();
+                if (pf_have && pf_then_stores >= 4)
+                    vmem_wait_keep<4>();
+                else if (pf_have && pf_then_stores >= 2)
+                    vmem_wait_keep<2>();
+                else
+                    vmem_drain();
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const u32x4 w = s_pfx[(wave * R + r) * 64 + lane];
@@ -232,28 +240,36 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
         int32_t row_prefix[R];
         int32_t row_total[R];
         if (have_new) {
-            if (!full) {  // the tail block, or unaligned pointers: item by item
+            if (!full) {
+                // the tail block, or unaligned pointers: item by item, from positions held
+                // inside the array, so that all loads go out before the first wait
+                uint32_t kv[R][E];
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    uint32_t kv[E];
+                for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int k = 0; k < E; ++k) {
                         const int64_t p = lane0 + int64_t(r) * ROW + k;
-                        raw[r][k] = (p < n) ? x[p] : T(0);
-                        kv[k] = (p < n && keep) ? uint32_t(keep[p]) : 0u;
+                        const int64_t q = p < n ? p : n - 1;
+                        raw[r][k] = x[q];
+                        kv[r][k] = keep ? uint32_t(keep[q]) : 0u;
                     }
-                    // with the prefetch: the row's loads complete inside this partial-block
-                    // path, so the compiler's waits for them stay off full blocks
-                    if constexpr (kPrefetch) {
+                // with the prefetch: the loads complete inside this partial-block path, so
+                // the compiler's waits for them stay off full blocks
+                if constexpr (kPrefetch) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
                         complete_loads(raw[r]);
 #pragma unroll
-                        for (int k = 0; k < E; ++k) asm volatile("" : "+v"(kv[k]));
+                        for (int k = 0; k < E; ++k) asm volatile("" : "+v"(kv[r][k]));
                     }
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
                     uint32_t m = 0;
 #pragma unroll
                     for (int k = 0; k < E; ++k) {
                         const int64_t p = lane0 + int64_t(r) * ROW + k;
-                        if (p < n && (keep ? (kv[k] != 0) : (raw[r][k] != T(0)))) m |= 1u << k;
+                        if (p < n && (keep ? (kv[r][k] != 0) : (raw[r][k] != T(0)))) m |= 1u << k;
                     }
                     bits[r] = m;
                 }
@@ -314,47 +330,38 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
         if (have_pend) {
             const VB base = s_block_prefix[parity];
             T* stage = s_stage[wave];
+            const int64_t g0 = base + p_row0[0];  // first position of this wave's items
+            const int32_t shift = int32_t((reinterpret_cast<uintptr_t>(out + g0) % 128) / sizeof(T));
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const int64_t g0 = base + p_row0[r];  // first position of this wave-row's items
                 const uint32_t m = p_bits[r];
-                if (!out_vec) {  // out not 16-byte aligned: item by item
-                    int32_t before = 0;
-#pragma unroll
-                    for (int k = 0; k < E; ++k) {
-                        if ((m >> k) & 1u) out[g0 + p_lane[r] + before] = p_x[r][k];
-                        before += int32_t((m >> k) & 1u);
-                    }
-                    continue;
-                }
-                // stage the row's kept items at their offsets from the aligned
-                // vector below g0, then write whole aligned vectors (and the
-                // partial vectors at both ends item by item)
-                const int32_t shift = int32_t(g0 & int64_t(E - 1));
-                int32_t at = shift + p_lane[r];
+                int32_t at = shift + (p_row0[r] - p_row0[0]) + p_lane[r];
 #pragma unroll
                 for (int k = 0; k < E; ++k) {
                     if ((m >> k) & 1u) stage[at] = p_x[r][k];
                     at += int32_t((m >> k) & 1u);
                 }
-                wave_lds_sync();
-                const int32_t span = shift + p_rowcnt[r];  // staged items occupy [shift, span)
-                T* dst = out + (g0 - shift);
-                for (int32_t c = lane * E; c < span; c += 64 * E) {
-                    if (c >= shift && c + E <= span) {
-                        T v[E];
-                        __builtin_memcpy(v, stage + c, 16);
-                        u32x4 w;
-                        __builtin_memcpy(&w, v, 16);
-                        *reinterpret_cast<u32x4*>(dst + c) = w;
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < E; ++k)
-                            if (c + k >= shift && c + k < span) dst[c + k] = stage[c + k];
-                    }
-                }
-                wave_lds_sync();
             }
+            wave_lds_sync();
+            const int32_t span = shift + p_total;  // staged items occupy [shift, span)
+            T* dst = out + (g0 - shift);
+            for (int32_t c = lane * E; c < span; c += 64 * E) {
+                if (c >= shift && c + E <= span) {
+                    T v[E];
+                    __builtin_memcpy(v, stage + c, 16);
+                    u32x4 w;
+                    __builtin_memcpy(&w, v, 16);
+                    *reinterpret_cast<u32x4*>(dst + c) = w;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < E; ++k)
+                        if (c + k >= shift && c + k < span) dst[c + k] = stage[c + k];
+                }
+            }
+            wave_lds_sync();
+            // rounds of the loop in which some lane holds a whole vector
+            const int32_t v0 = (shift + E - 1) / E, v1 = span / E;
+            pf_then_stores = (v1 > v0) ? (v1 - 1) / 64 - v0 / 64 + 1 : 0;
         }
 
         // -- 6. the new block becomes the pending one
@@ -362,12 +369,12 @@ __global__ void __launch_bounds__(TT) compact_kernel(ScanArgs a)
         if (have_new) {
             p_i = i;
             p_agg = agg;
+            p_total = row_prefix[R - 1] + row_total[R - 1];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 p_bits[r] = bits[r];
                 p_row0[r] = wave_prefix + row_prefix[r];
                 p_lane[r] = lane_prefix[r];
-                p_rowcnt[r] = row_total[r];
 #pragma unroll
                 for (int k = 0; k < E; ++k) p_x[r][k] = raw[r][k];
             }
