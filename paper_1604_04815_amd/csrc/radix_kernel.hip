@@ -13,6 +13,17 @@
 // its own LDS histogram (LDS atomics), the wave histograms are summed into
 // the workgroup's G x 2^bits table, and at the end the table leaves in
 // digit-major order, G consecutive counts per digit.
+//
+// The reads of the keys bound it (the LDS atomics take about 11 of 38 us at
+// 50 million keys).  So the next round's vectors, of this block or the next
+// one, are loaded before this round is counted; two sets of histograms leave
+// one barrier per block; and vectors are read at any alignment of the keys
+// and of the blocks.  Measured with the scan of the counts, int32 keys, 8
+// bits, before and after: 50 million keys in blocks of 4096 54.7 / 53.3 us,
+// the same off a 16-byte line 84.7 / 51.5, 300 million 304 / 296 (4.1 TB/s
+// of keys), 50 million in blocks of 1000 with 4 bits 67 / 59.  Four vectors
+// in flight at 256 threads take 252 against 245 us where the reads already
+// run at the copy rate (400 million keys in blocks of 100 000).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,10 +34,20 @@ namespace lscan {
 namespace {
 
 constexpr int kHistThreads = 256;
-constexpr int kHistWaves = kHistThreads / 64;
+constexpr int kHistThreadsWide = 1024;
 constexpr int kMaxDigits = 256;
 
+// Launches of at most two workgroups per CU with large blocks take 1024
+// threads and four vectors in flight per thread: 256 threads leave the CUs
+// short of loads (int32 keys, 48 blocks of 2^20: 82 against 195 us; 382:
+// 253 / 356; 501 blocks of 100 000: 38 / 44).  With more workgroups the chip
+// is full either way and the 1024 threads of a block wait on its barrier
+// (763 blocks of 65 536: 41 against 37 us).
+constexpr int64_t kHistWideGroups = 512;
+constexpr int64_t kHistWideItems = 32768;
+
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+typedef u32x4v VecU __attribute__((aligned(4)));  // keys need no more than their own alignment
 
 template <class K>
 __device__ __forceinline__ uint32_t digit_of(K key, int shift, uint32_t mask)
@@ -34,74 +55,99 @@ __device__ __forceinline__ uint32_t digit_of(K key, int shift, uint32_t mask)
     return uint32_t(uint64_t(key) >> shift) & mask;
 }
 
-template <class K>
-__global__ void __launch_bounds__(kHistThreads) digit_count_kernel(RadixArgs a)
+template <class K, int THREADS>
+__global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
 {
-    __shared__ uint32_t s_wave_hist[kHistWaves][kMaxDigits];
-    extern __shared__ uint32_t s_table[];  // [G][digits]
+    constexpr int kHistWaves = THREADS / 64;
+    __shared__ uint32_t s_wave_hist[2][kHistWaves][kMaxDigits];  // of this block and the next
+    extern __shared__ uint32_t s_table[];                        // [G][digits + 1]
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int digits = 1 << a.bits;
+    const int row = digits + 1;  // a column of the table is read by consecutive lanes
     const uint32_t mask = uint32_t(digits - 1);
     const int64_t b0 = int64_t(blockIdx.x) * a.group;
-    const int64_t gcount = (a.num_blocks - b0 < a.group) ? (a.num_blocks - b0) : a.group;
+    const int gcount = int((a.num_blocks - b0 < a.group) ? (a.num_blocks - b0) : a.group);
     const K* keys = static_cast<const K*>(a.keys);
     constexpr int E = 16 / int(sizeof(K));
+    constexpr int64_t kStride = int64_t(THREADS) * E;
+    constexpr int kVecs = THREADS == kHistThreads ? 2 : 4;  // vectors of one round per thread
 
-    for (int d = tid; d < kHistWaves * kMaxDigits; d += kHistThreads) (&s_wave_hist[0][0])[d] = 0;
+    for (int d = tid; d < 2 * kHistWaves * kMaxDigits; d += THREADS) (&s_wave_hist[0][0][0])[d] = 0;
     __syncthreads();
 
-    for (int64_t g = 0; g < gcount; ++g) {
-        const int64_t lo = (b0 + g) * a.block_items;
-        const int64_t hi = (lo + a.block_items < a.n) ? lo + a.block_items : a.n;
-        uint32_t* hist = s_wave_hist[wave];
-        int64_t p = lo;
-        if (a.vec_ok) {  // 16-byte vectors over the aligned body of the block
-            const int64_t v_end = lo + ((hi - lo) / E) * E;
-            const int64_t stride = int64_t(kHistThreads) * E;
-            int64_t q = lo + int64_t(tid) * E;
-            // four vectors in flight per thread before their counts go to LDS
-            for (; q + 3 * stride < v_end; q += 4 * stride) {
-                u32x4v w[4];
+    // One round: kVecs vectors per thread from key `base` on.  Addresses past
+    // the array's last whole vector are drawn back to it, their keys are not
+    // counted; an array without a whole vector is not read as vectors.
+    const int64_t last_vec = a.n - E;
+    VecU w[kVecs];
+    auto load_round = [&](int64_t base, int64_t end) {
+        const K* from = keys + base + tid * E;
+        if (base + kVecs * kStride <= end) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(keys + q + u * stride));
+            for (int u = 0; u < kVecs; ++u)
+                w[u] = __builtin_nontemporal_load(reinterpret_cast<const VecU*>(from + u * kStride));
+            return;
+        }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < kVecs; ++u) {
+            if (base + u * kStride >= end) break;
+            const int64_t q = base + u * kStride + tid * E;
+            w[u] = __builtin_nontemporal_load(reinterpret_cast<const VecU*>(keys + (q < last_vec ? q : last_vec)));
+        }
+    };
+    auto block_end = [&](int64_t first) { return first + a.block_items < a.n ? first + a.block_items : a.n; };
+
+    int64_t lo = b0 * a.block_items;
+    if (last_vec >= 0) load_round(lo, block_end(lo));
+    for (int g = 0; g < gcount; ++g, lo += a.block_items) {
+        const int64_t hi = block_end(lo);
+        const int64_t v_end = hi - (hi - lo) % E;
+        uint32_t* hist = s_wave_hist[g & 1][wave];
+        for (int64_t base = lo; base < v_end; base += kVecs * kStride) {
+            u32x4v now[kVecs];
+#pragma unroll
+            for (int u = 0; u < kVecs; ++u) now[u] = w[u];
+            // the next round's vectors are in flight while this one is counted
+            const bool full = base + kVecs * kStride <= v_end;
+            const bool more = base + kVecs * kStride < v_end;
+            if (more || g + 1 < gcount) load_round(more ? base + kVecs * kStride : hi, more ? v_end : block_end(hi));
+#pragma unroll
+            for (int u = 0; u < kVecs; ++u) {
+                if (full || base + u * kStride + tid * E < v_end) {
                     K k[E];
-                    __builtin_memcpy(k, &w[u], 16);
+                    __builtin_memcpy(k, &now[u], 16);
 #pragma unroll
                     for (int e = 0; e < E; ++e) atomicAdd(&hist[digit_of(k[e], a.shift, mask)], 1u);
                 }
             }
-            for (; q < v_end; q += stride) {
-                u32x4v w = __builtin_nontemporal_load(reinterpret_cast<const u32x4v*>(keys + q));
-                K k[E];
-                __builtin_memcpy(k, &w, 16);
-#pragma unroll
-                for (int e = 0; e < E; ++e) atomicAdd(&hist[digit_of(k[e], a.shift, mask)], 1u);
-            }
-            p = v_end;
         }
-        for (int64_t q = p + tid; q < hi; q += kHistThreads) atomicAdd(&hist[digit_of(keys[q], a.shift, mask)], 1u);
+        if (v_end + tid < hi) atomicAdd(&hist[digit_of(keys[v_end + tid], a.shift, mask)], 1u);
+        // The other histogram is clear here: its last counts were summed
+        // before this barrier by every thread.
         __syncthreads();
-        for (int d = tid; d < digits; d += kHistThreads) {
+        for (int d = tid; d < digits; d += THREADS) {
             uint32_t c = 0;
 #pragma unroll
-            for (int w = 0; w < kHistWaves; ++w) {
-                c += s_wave_hist[w][d];
-                s_wave_hist[w][d] = 0;
+            for (int v = 0; v < kHistWaves; ++v) {
+                c += s_wave_hist[g & 1][v][d];
+                s_wave_hist[g & 1][v][d] = 0;
             }
-            s_table[g * digits + d] = c;
+            s_table[g * row + d] = c;
         }
-        __syncthreads();
     }
+    __syncthreads();
 
     // digit-major: for each digit, the G counts of this group's blocks
-    for (int64_t t = tid; t < int64_t(digits) * gcount; t += kHistThreads) {
-        const int64_t d = t / gcount, g = t - d * gcount;
-        a.counts[d * a.num_blocks + b0 + g] = int64_t(s_table[g * digits + d]);
+    const int dstep = THREADS / gcount, gstep = THREADS % gcount;
+    int d = tid / gcount, g = tid % gcount;
+    for (; d < digits; d += dstep, g += gstep) {
+        if (g >= gcount) {
+            g -= gcount;
+            if (++d >= digits) break;
+        }
+        a.counts[int64_t(d) * a.num_blocks + b0 + g] = int64_t(s_table[g * row + d]);
     }
 }
 
@@ -110,14 +156,15 @@ __global__ void __launch_bounds__(kHistThreads) digit_count_kernel(RadixArgs a)
 hipError_t launch_digit_counts(const RadixArgs& a, hipStream_t stream)
 {
     const int64_t groups = (a.num_blocks + a.group - 1) / a.group;
-    const size_t table_bytes = size_t(a.group) * size_t(1 << a.bits) * sizeof(uint32_t);
+    const size_t table_bytes = size_t(a.group) * size_t((1 << a.bits) + 1) * sizeof(uint32_t);
     (void)hipGetLastError();
-    if (a.key_bytes == 4)
-        hipLaunchKernelGGL(digit_count_kernel<uint32_t>, dim3(unsigned(groups)), dim3(kHistThreads), table_bytes,
-                           stream, a);
-    else
-        hipLaunchKernelGGL(digit_count_kernel<uint64_t>, dim3(unsigned(groups)), dim3(kHistThreads), table_bytes,
-                           stream, a);
+    const bool wide = groups <= kHistWideGroups && a.block_items >= kHistWideItems;
+    auto kernel = a.key_bytes == 4 ? (wide ? digit_count_kernel<uint32_t, kHistThreadsWide>
+                                           : digit_count_kernel<uint32_t, kHistThreads>)
+                                   : (wide ? digit_count_kernel<uint64_t, kHistThreadsWide>
+                                           : digit_count_kernel<uint64_t, kHistThreads>);
+    hipLaunchKernelGGL(kernel, dim3(unsigned(groups)), dim3(wide ? kHistThreadsWide : kHistThreads), table_bytes,
+                       stream, a);
     return hipGetLastError();
 }
 

@@ -17,10 +17,9 @@ struct RadixArgs {
     int32_t key_bytes;     // 4 or 8
     int32_t shift;         // digit = (key >> shift) & (2^bits - 1)
     int32_t bits;          // 1 .. 8
-    int32_t vec_ok;        // keys 16-byte aligned and block_items a multiple of 16 / key_bytes
 };
 
-// Enqueue the digit-count kernel; G * 2^bits * 4 bytes of LDS per workgroup.
+// Enqueue the digit-count kernel; G * (2^bits + 1) * 4 bytes of LDS per workgroup.
 hipError_t launch_digit_counts(const RadixArgs& a, hipStream_t stream);
 
 }  // namespace lscan

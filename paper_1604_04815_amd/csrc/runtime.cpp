@@ -1727,12 +1727,11 @@ lscan_status lscan_radix_offsets(const void* keys, int64_t n, lscan_dtype dt, in
     // enough workgroups to fill the device, each writing a run of counts per
     // digit; the table of a workgroup stays within 32 KiB of LDS
     const int64_t want = (m + 1023) / 1024;
-    a.group = std::max<int64_t>(1, std::min<int64_t>(want, 8192 / digits));
+    a.group = std::max<int64_t>(1, std::min<int64_t>(want, 8192 / (digits + 1)));
     a.counts = offsets;
     a.key_bytes = kb;
     a.shift = shift;
     a.bits = bits;
-    a.vec_ok = (reinterpret_cast<uintptr_t>(keys) % 16 == 0 && block_items % (16 / kb) == 0) ? 1 : 0;
     hipError_t e = lscan::launch_digit_counts(a, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return device_error(e);
     // the offsets: exclusive +-scan of the digit-major counts, in place

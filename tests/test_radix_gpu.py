@@ -86,3 +86,15 @@ def test_radix_offsets_full_size(gpu_lib):
     log("[radix] full size 2^28")
     got = device_offsets(gpu_lib, kbits.view(np.int32), "int32", 0, 8, 16_384)
     assert np.array_equal(got, oracle.radix_offsets(kbits, 0, 8, 16_384))
+
+@pytest.mark.parametrize("dtype,block,off_items", [("int32", 2048, 0), ("int32", 2049, 1), ("int32", 3, 3),
+                                                   ("int64", 1023, 1), ("int64", 1, 0), ("int32", 32_768, 2),
+                                                   ("int64", 40_001, 1)])
+def test_radix_rounds_and_ends(gpu_lib, dtype, block, off_items):
+    # blocks of one round of loads and one key more or less, blocks smaller than a
+    # vector, the wide workgroups' first block size; keys on every alignment of
+    # their own size; arrays that end within, at and one past a vector
+    for n in (2, 4, 5, block, 3 * block + 1, 70 * block - 1):
+        kbits, host = keys_for(dtype, n, seed=n)
+        got = device_offsets(gpu_lib, host, dtype, 9, 8, block, offset_items=off_items)
+        assert np.array_equal(got, oracle.radix_offsets(kbits, 9, 8, block)), n
