@@ -138,3 +138,13 @@ def test_compact_full_size(gpu_lib):
     log("[compact] full size 2^28")
     got, count = run(gpu_lib, x, keep, "int32")
     check(got, count, x, keep, "int32", "2^28")
+
+
+@pytest.mark.parametrize("dtype,n", [("int32", 8191), ("int32", 8193), ("int32", 1 << 21), ("int32", (1 << 21) + 1),
+                                     ("int64", 4097), ("int64", 1 << 20), ("int64", (1 << 20) + 1)])
+def test_compact_small_tiles(gpu_lib, dtype, n):
+    # one small tile and one item more or less; the largest small array and the next
+    x = items(dtype, n, seed=n)
+    for keep in (flags(n, 0.6, seed=n + 2), None):
+        got, count = run(gpu_lib, x, keep, dtype)
+        check(got, count, x, keep, dtype, f"{dtype} n={n}")
