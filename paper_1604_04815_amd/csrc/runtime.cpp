@@ -701,17 +701,18 @@ constexpr int64_t kLineGridBytes = int64_t(256) << 20;  // of output
 int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n, bool* store_vec)
 {
     const uintptr_t xa = reinterpret_cast<uintptr_t>(x), ya = reinterpret_cast<uintptr_t>(y);
-    const int64_t ib = k.in_bytes, ob = k.out_bytes;
-    const int64_t step = std::max<int64_t>(16 / ib, 1), line = std::max<int64_t>(128 / ob, 1);
-    const int64_t first = int64_t(xa % 16) / ib;
-    auto out_offset = [&](int64_t ph, int64_t unit) { return (int64_t(ya % 128) + 128 * ob - ph * ob) % unit; };
+    const int64_t ob = k.out_bytes, L = k.tile_elems;
+    // (batches do this for every array: 32-bit divisions, none for arrays of one block)
+    const int64_t step = std::max<int32_t>(16 / k.in_bytes, 1), line = std::max<int32_t>(128 / k.out_bytes, 1);
+    const int64_t first = int32_t(xa % 16) / k.in_bytes;
+    auto out_offset = [&](int64_t ph, uint32_t unit) { return uint32_t(ya - uint64_t(ph * ob)) % unit; };
+    auto blocks = [&](int64_t ph) { return n + ph <= L ? 1 : (n + ph + L - 1) / L; };
     int64_t vec = -1;  // the first position whose outputs start on 16 bytes
     for (int64_t ph = first; ph < first + line; ph += step) {
         if (out_offset(ph, 16) != 0) continue;
         if (vec < 0) vec = ph;
         if (out_offset(ph, 128) == 0) {
-            const int64_t L = k.tile_elems;
-            if (n * ob >= kLineGridBytes || (n + ph + L - 1) / L == (n + vec + L - 1) / L) vec = ph;
+            if (n * ob >= kLineGridBytes || blocks(ph) == blocks(vec)) vec = ph;
             break;
         }
     }
@@ -731,12 +732,12 @@ int64_t batch_phase(const KernelEntry& k, const lscan_array& arr, bool* stage_y)
     return (store_vec || *stage_y) ? ph : -1;
 }
 
-// Blocks of one array of a batch: its n elements after its alignment phase.
-int64_t batch_blocks(const KernelEntry& k, const lscan_array& arr, int64_t L)
+// Blocks of one array of a batch: its n elements after its grid phase.
+int64_t batch_blocks(int64_t n, int64_t phase, int64_t L)
 {
-    if (arr.n <= 0) return 0;
-    bool stage_y;
-    return (arr.n + std::max<int64_t>(batch_phase(k, arr, &stage_y), 0) + L - 1) / L;
+    if (n <= 0) return 0;
+    const int64_t end = n + std::max<int64_t>(phase, 0);
+    return end <= L ? 1 : (end + L - 1) / L;
 }
 
 // Choose the kernel and grid, size the workspace, run the co-residency test
@@ -810,7 +811,9 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
     const int64_t L = k.tile_elems;
     int64_t M = 0;
     if (r.mode == kModeBatched) {
-        for (int64_t i = 0; i < r.num_arrays; ++i) M += batch_blocks(k, r.arrays[i], L);
+        bool stage_y = false;
+        for (int64_t i = 0; i < r.num_arrays; ++i)
+            M += batch_blocks(r.arrays[i].n, batch_phase(k, r.arrays[i], &stage_y), L);
     } else {
         M = (r.n + phase + L - 1) / L;
     }
@@ -857,7 +860,7 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
             bool stage_y = false;
             ws->desc_host[i].phase = batch_phase(k, r.arrays[i], &stage_y);
             ws->desc_host[i].stage_y = stage_y ? 1 : 0;
-            first += batch_blocks(k, r.arrays[i], L);
+            first += batch_blocks(r.arrays[i].n, ws->desc_host[i].phase, L);
         }
         ws->desc_host[r.num_arrays] = BatchArray{nullptr, nullptr, 0, first, 0, 0};
         e = hipMemcpyAsync(ws->desc, ws->desc_host, desc_entries * sizeof(BatchArray), hipMemcpyHostToDevice,

@@ -533,6 +533,10 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     constexpr bool kBlocked = kPrefetch && E * sizeof(Out) == 16 &&
                               ((MODE == kModePlain && blocked_lanes<BaseOp>::value) ||
                                (MODE == kModeSegmented && blocked_segmented<BaseOp>::value));
+    // partial blocks choose how to load row by row (lane-blocked ones wave by wave),
+    // but not in segmented scans: 25 M int32 in 2^20 segments take 56.9 us so, 53.1
+    // without, though 40 000 in 300 gain (7.5 -> 6.9)
+    constexpr bool kRowVec = MODE != kModeSegmented;
     constexpr int64_t kLaneElems = kBlocked ? int64_t(R) * E : E;
     constexpr int64_t kRowStep = kBlocked ? E : ROW;
     __shared__ __attribute__((aligned(16))) u32x4 s_tr[kBlocked ? T * R : 1];
@@ -777,23 +781,30 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                     for (int r = 0; r < R; ++r) load_vector<In, E>(x + lane0 + int64_t(r) * kRowStep, raw[r]);
                 }
             } else {
-                // an array's first or last block, or one that cannot use vectors: in
-                // batches, where such blocks are many, whole rows of the wave (a
-                // wave-uniform choice) still move as vectors; the others element by
-                // element, from positions held inside the array, so that no load hangs
-                // on a condition and all go out before the first wait.  (With a wait
-                // per row, the one such block of a ragged array took 5 us of its scan.)
+                // an array's first or last block, or one that cannot use vectors: whole
+                // rows of the wave (a wave-uniform choice) move as vectors, rows past the
+                // array are not read, and the others go element by element, from
+                // positions held inside the array, so that no lane's load hangs on a
+                // condition.  Bound by the latency of that one block: plain float32 add
+                // of 950 428 elements off a line 11.0 us with every row element by
+                // element, 8.6 so; 2024 bfloat16 arrays of 2769 80.5 / 74.5;
+                // compensated, 950 428 off a line 16.8 / 11.6.  (Vectors
+                // from positions held inside, with the ends put in place by selects,
+                // took registers from the full blocks: 2^20 int32 5.7 -> 6.3 us.)
                 const int64_t row0 = tile0 + int64_t(wave) * (R * ROW);
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int64_t rs = row0 + int64_t(r) * ROW;
-                    if (MODE == kModeBatched && vec_ok && rs >= ph && rs + ROW <= n) vrow |= 1u << r;
+                    const int64_t rs = kBlocked ? row0 : row0 + int64_t(r) * ROW;
+                    if (kRowVec && vec_ok && rs >= ph && rs + (kBlocked ? R : 1) * ROW <= n) vrow |= 1u << r;
                 }
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int64_t p0 = lane0 + int64_t(r) * kRowStep;
-                    if (MODE == kModeBatched && ((vrow >> r) & 1u)) {
+                    if (kRowVec && ((vrow >> r) & 1u)) {
                         load_vector<In, E>(x + p0, raw[r]);
+                    } else if (kRowVec && row0 + (kBlocked ? 0 : int64_t(r) * ROW) >= n) {
+#pragma unroll
+                        for (int k = 0; k < E; ++k) raw[r][k] = In{};
                     } else {
 #pragma unroll
                         for (int k = 0; k < E; ++k) {

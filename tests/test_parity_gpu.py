@@ -319,3 +319,18 @@ def test_block_grid_starts_on_a_line_of_y(gpu_lib, dtype, op):
                 what = f"line grid {dtype}/{op} n={n} x+{xo} y+{yo} excl={excl}"
                 compare(to_host(out[yo:yo + n]), x, dtype, op, excl, what=what)
                 assert bool((out[:yo] == 7).all()) and bool((out[yo + n:] == 7).all()), f"{what}: writes outside y"
+
+
+@pytest.mark.parametrize("dtype,comp", [("int32", False), ("float32", True), ("bfloat16", False), ("int64", False)])
+def test_partial_block_rows(gpu_lib, dtype, comp):
+    # the last block ends before, at and after a row and a lane vector of one
+    # wave; the first starts off a line; arrays of less than a row
+    tile = 512 * 8 * 4
+    for n in (1, 3, 255, 256, 257, 2048, 2049, tile - 1, tile + 1, tile + 511, 3 * tile + 1025, 2 * tile + 2049):
+        x = make_input(dtype, "add", n, seed=n)
+        for off in (0, 1, 3):
+            buf = torch.empty(n + off, dtype=to_device(x, dtype).dtype, device="cuda")
+            buf[off:] = to_device(x, dtype)
+            for params in (None, gpu_lib.Params(512, 8, 1, 0)):
+                y = gpu_lib.inclusive(buf[off:], "add", compensated=comp, params=params)
+                compare(to_host(y), x, dtype, "add", False, compensated=comp, what=f"{dtype} n={n} x+{off} {params}")
