@@ -279,8 +279,8 @@ lscan_status lscan_tile_shape(int32_t idx, lscan_params *out);
  * kind; set replaces them (e.g. from an autotuner).  The defaults are those
  * of large arrays: while an operator's parameters are the library's own,
  * plain add / max / min scans of at most 32 MiB of input, segmented ones of at
- * most 4 MiB and running argmax / argmin of at most 8 MiB run smaller tiles of
- * 1024- or 512-thread workgroups (they
+ * most 4 MiB, running argmax / argmin of at most 8 MiB and compactions of at
+ * most 8 MiB of items run smaller tiles of 1024- or 512-thread workgroups (they
  * finish sooner when the array cannot fill the device); other parameters, once set, apply to every size. */
 lscan_status lscan_get_params(lscan_dtype dt, lscan_op op, uint32_t flags,
                               int32_t kind, lscan_params *out);
@@ -393,9 +393,9 @@ lscan_status lscan_scan_custom(const lscan_custom_kernel *kernel,
  * as the next use of the paper's inter-block hand-off (Section 4.3): one
  * persistent launch runs the whole search.  The edges of each level's
  * frontier are cut into equal chunks taken cyclically by a co-resident
- * grid; each chunk claims the undiscovered endpoints of its edges (an
- * atomic or on a visited bitmap: the lane that sets a vertex's bit finds
- * it), publishes how many
+ * grid; each chunk claims the undiscovered endpoints of its edges (levels
+ * with very many edges mark them instead, and a sweep over the vertices
+ * collects the marks), publishes how many
  * vertices and edges it found in epoch-tagged flag words, and obtains where
  * they go in the next frontier from the values published before it (the
  * window fold of the scan) -- no shared queue-tail counter.  Levels end
