@@ -58,6 +58,7 @@
 
 #include "kernel_table.hpp"
 #include "scan_ops.hpp"
+#include "segment_search.hpp"
 
 namespace lscan {
 
@@ -372,34 +373,28 @@ typedef const BatchArray __attribute__((address_space(4))) CBatchArray;
 
 // First indices k in [0, S) with off[k] >= v0 (and >= v1), or S, found by one
 // wave: 64 probes a round cut the range by 65, so 2^20 offsets take four
-// rounds.  Offsets that decrease somewhere give some index in [0, S].
+// rounds (segment_search.hpp).  Offsets that decrease somewhere give some index
+// in [0, S]; no offset outside [0, S) is read.
 __device__ __forceinline__ void wave_lower_bounds(const int64_t* off, int64_t S, int64_t v0, int64_t v1, int lane,
                                                   int64_t& k0, int64_t& k1)
 {
-    int64_t lo[2] = {0, 0}, hi[2] = {S, S};
+    OffsetRange r[2] = {{0, S}, {0, S}};
     const int64_t v[2] = {v0, v1};
-    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+    while (range_open(r[0]) || range_open(r[1])) {
         int64_t x[2], step[2];
         bool probe[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {  // both probes in flight
-            step[q] = (hi[q] - lo[q] + 64) / 65;  // 1 once at most 65 indices are left
-            const int64_t p = lo[q] + (lane + 1) * step[q] - 1;
-            probe[q] = p < hi[q];
+            step[q] = probe_step(r[q]);
+            const int64_t p = probe_index(r[q], step[q], lane);
+            probe[q] = probe_reads(r[q], p);
             x[q] = probe[q] ? off[p] : 0;
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int64_t below = __popcll(__ballot(probe[q] && x[q] < v[q]));
-            const int64_t first = lo[q] + below * step[q];
-            const int64_t end = first + step[q] - 1;  // the first probe not below, if there is one
-            const bool inside = below < 64 && end < hi[q];
-            lo[q] = first < hi[q] ? first : hi[q];
-            if (inside) hi[q] = end;
-        }
+        for (int q = 0; q < 2; ++q) r[q] = narrowed(r[q], step[q], __popcll(__ballot(probe[q] && x[q] < v[q])));
     }
-    k0 = lo[0];
-    k1 = lo[1];
+    k0 = r[0].lo;
+    k1 = r[1].lo;
 }
 
 // The launch's epoch tag.  The host counts the launches on a workspace and hands

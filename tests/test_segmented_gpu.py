@@ -159,3 +159,20 @@ def test_segment_ranges(gpu_lib, segments, table):
             info = gpu_lib.lscan_last_launch()
             assert (info.num_blocks > 2 * info.grid) == table
             compare(to_host(y), x, dtype, op, excl, offsets=off, what=f"S={segments} table={table} {dtype}/{op}/{excl}")
+
+
+@pytest.mark.parametrize("segments", [64, 65, 66, 4225, 4289])
+def test_first_block_holds_the_heads(gpu_lib, segments):
+    # the two searches of the first block end rounds apart when it holds most of the
+    # heads (short or empty segments); the offsets start their allocation
+    n = 1000 if segments < 100 else 5000
+    g = np.random.default_rng(segments)
+    cuts = np.sort(g.integers(0, n * 4 // 5, segments - 1))
+    off = np.concatenate([[0], cuts, [n]]).astype(np.int64)
+    x = make_input("int32", "add", n, seed=segments)
+    log(f"[seg] first block S={segments} n={n}")
+    for excl in (False, True):
+        got = run(gpu_lib, x, off, "int32", "add", excl)
+        info = gpu_lib.lscan_last_launch()
+        assert info.num_blocks <= 2 * info.grid
+        compare(got, x, "int32", "add", excl, offsets=off, what=f"first block S={segments}/{excl}")
