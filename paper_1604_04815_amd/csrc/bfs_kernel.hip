@@ -89,8 +89,9 @@ struct BfsShared {
     int32_t stage[2][K];     // discovered vertices that have edges: the chunk being
                              // claimed and the one waiting to be placed
     int64_t wave_tot[kWaves];
-    uint64_t found_e;        // edges of the staged vertices
-    uint32_t found;          // staged vertices
+    uint64_t found_e[2];     // edges of the vertices in stage[] (cleared for the next chunk
+                             // while other waves still read this chunk's)
+    uint32_t found[2];       // vertices in stage[]
     uint32_t found2[2];      // vertices found by a solo level, alternating
     uint32_t found_all;      // vertices this workgroup discovered in the current level
     uint32_t bad;            // malformed entries this workgroup met
@@ -893,14 +894,14 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
     if (tid == 0) {
         s.bad = (wg == 0 && src_deg < 0) ? 1u : 0u;
         s.found_all = 0;
-        s.found = 0;
+        s.found[0] = 0;
     }
     __syncthreads();
-    if (decreasing) atomicAdd(&s.found, decreasing);
+    if (decreasing) atomicAdd(&s.found[0], decreasing);
     __syncthreads();
 
     uint32_t tag = a.base_tag + 1u;
-    uint32_t v0[kBarrierWords] = {0u, 0u, 0u, s.found};
+    uint32_t v0[kBarrierWords] = {0u, 0u, 0u, s.found[0]};
     bool ok = grid_barrier(a, s, tag, v0);
     const int64_t bad_rows = s.res[3];
     if (ok && bad_rows > 0) {
@@ -987,8 +988,8 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
                 const ChunkRange cr = frontier_range<1>(fr, chunk_head<1>(fr, c));
                 frontier_to_lds<1>(fr, s, hb, c, cr, frontier_entry(fr, cr));
                 if (tid == 0) {
-                    s.found = 0;
-                    s.found_e = 0;
+                    s.found[sb] = 0;
+                    s.found_e[sb] = 0;
                 }
                 __syncthreads();
 
@@ -1047,18 +1048,18 @@ __global__ void __launch_bounds__(kBfsThreads) bfs_kernel(BfsArgs a)
                     uint32_t base = 0;
                     if (lane == 0) {
                         if (m_all) atomicAdd(&s.found_all, uint32_t(__popcll(m_all)));
-                        if (m) base = atomicAdd(&s.found, uint32_t(__popcll(m)));
+                        if (m) base = atomicAdd(&s.found[sb], uint32_t(__popcll(m)));
                     }
                     base = __builtin_amdgcn_readlane(base, 0);
                     if (keep) {
                         const uint32_t pos = base + lanes_before(m);  // < K: one discovery per edge at most
                         s.stage[sb][pos] = v[p];
-                        atomicAdd(reinterpret_cast<unsigned long long*>(&s.found_e), (unsigned long long)dv[p]);
+                        atomicAdd(reinterpret_cast<unsigned long long*>(&s.found_e[sb]), (unsigned long long)dv[p]);
                     }
                 }
                 __syncthreads();
-                A_n = uniform(s.found);
-                A_e = uniform(int64_t(s.found_e));
+                A_n = uniform(s.found[sb]);
+                A_e = uniform(int64_t(s.found_e[sb]));
 
                 // (c) publish (edges, vertices) packed, at once
                 if (wave == 0) publish_slot(a.slots + 2 * c, (A_e << kBfsCountBits) | A_n, tag, lane);

@@ -346,3 +346,30 @@ def test_small_levels_by_one_workgroup(gpu_lib, fan):
     log(f"[bfs] chain and fan {fan}")
     levels, parents, stats = run(gpu_lib, row, col, 0)
     check(row, col, 0, levels, parents, stats, f"fan {fan}")
+
+
+@pytest.mark.parametrize("with_parents", [True, False])
+def test_many_chunks_per_workgroup(gpu_lib, with_parents):
+    # two levels in a row of 1.6 to 1.9 million edges, fewer than a quarter of the
+    # vertices, go chunk by chunk: over three chunks of 2048 edges for each of 256
+    # workgroups, so a workgroup claims a chunk while the one before waits to be
+    # placed; then a wide level and small ones
+    nv = 8_000_003
+    g = np.random.default_rng(43)
+    ids = g.permutation(nv - 1) + 1
+    from_, s, d, at = np.zeros(1, np.int64), [], [], 0
+    for edges, pool in ((400, 400), (300_000, 250_000), (1_850_000, 1_600_000), (1_750_000, 1_000_000), (3_000_000, 1000)):
+        s.append(g.choice(from_, edges))
+        d.append(g.choice(ids[at:at + pool], edges))
+        from_, at = np.unique(d[-1]), at + pool
+    s, d = np.concatenate(s), np.concatenate(d)
+    row, col = csr(s, d, nv)
+    want = oracle.bfs_levels(row, col, 0)
+    deg = np.diff(row)
+    per_level = [int(deg[want == k].sum()) for k in range(5)]
+    chunked = [e for e in per_level if e > 3 * 256 * 2048 and 4 * e < nv]
+    assert len(chunked) == 2 and any(4 * e >= nv and e >= 1 << 20 for e in per_level), per_level
+    log(f"[bfs] many chunks V={nv} edges per level {per_level}")
+    for _ in range(3):
+        levels, parents, stats = run(gpu_lib, row, col, 0, with_parents=with_parents)
+        check(row, col, 0, levels, parents, stats, "many chunks")
