@@ -23,7 +23,10 @@
 // the same off a 16-byte line 84.7 / 51.5, 300 million 304 / 296 (4.1 TB/s
 // of keys), 50 million in blocks of 1000 with 4 bits 67 / 59.  Four vectors
 // in flight at 256 threads take 252 against 245 us where the reads already
-// run at the copy rate (400 million keys in blocks of 100 000).
+// run at the copy rate (400 million keys in blocks of 100 000).  The LDS of a workgroup, 8 KiB of histograms and up to 32 KiB of
+// table, lets exactly four share a CU: 2^27 keys in blocks of 4096 are 1024
+// workgroups, all resident at once (122 us; 31 blocks in a padded table
+// instead of 32 160 us, for the 33 workgroups left over).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -60,13 +63,19 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
 {
     constexpr int kHistWaves = THREADS / 64;
     __shared__ uint32_t s_wave_hist[2][kHistWaves][kMaxDigits];  // of this block and the next
-    extern __shared__ uint32_t s_table[];                        // [G][digits + 1]
+    extern __shared__ uint32_t s_table[];                        // [G][digits]
 
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int digits = 1 << a.bits;
-    const int row = digits + 1;  // a column of the table is read by consecutive lanes
     const uint32_t mask = uint32_t(digits - 1);
+    // row g of the table is rotated by g, or by as many rows as 64 words hold: its rows
+    // are written and its columns read by consecutive lanes, and a padded row would
+    // take the 256-thread workgroups' LDS past a quarter of the CU's
+    const int rot = a.bits < 6 ? 6 - a.bits : 0;
+    auto entry = [&](int g, int d) -> uint32_t& {
+        return s_table[g * digits + int(uint32_t(d + (g >> rot)) & mask)];
+    };
     const int64_t b0 = int64_t(blockIdx.x) * a.group;
     const int gcount = int((a.num_blocks - b0 < a.group) ? (a.num_blocks - b0) : a.group);
     const K* keys = static_cast<const K*>(a.keys);
@@ -134,7 +143,7 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
                 c += s_wave_hist[g & 1][v][d];
                 s_wave_hist[g & 1][v][d] = 0;
             }
-            s_table[g * row + d] = c;
+            entry(g, d) = c;
         }
     }
     __syncthreads();
@@ -147,7 +156,7 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
             g -= gcount;
             if (++d >= digits) break;
         }
-        a.counts[int64_t(d) * a.num_blocks + b0 + g] = int64_t(s_table[g * row + d]);
+        a.counts[int64_t(d) * a.num_blocks + b0 + g] = int64_t(entry(g, d));
     }
 }
 
@@ -156,7 +165,7 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
 hipError_t launch_digit_counts(const RadixArgs& a, hipStream_t stream)
 {
     const int64_t groups = (a.num_blocks + a.group - 1) / a.group;
-    const size_t table_bytes = size_t(a.group) * size_t((1 << a.bits) + 1) * sizeof(uint32_t);
+    const size_t table_bytes = size_t(a.group) * size_t(1 << a.bits) * sizeof(uint32_t);
     (void)hipGetLastError();
     const bool wide = groups <= kHistWideGroups && a.block_items >= kHistWideItems;
     auto kernel = a.key_bytes == 4 ? (wide ? digit_count_kernel<uint32_t, kHistThreadsWide>

@@ -19,7 +19,7 @@ struct RadixArgs {
     int32_t bits;          // 1 .. 8
 };
 
-// Enqueue the digit-count kernel; G * (2^bits + 1) * 4 bytes of LDS per workgroup.
+// Enqueue the digit-count kernel; G * 2^bits * 4 bytes of LDS per workgroup.
 hipError_t launch_digit_counts(const RadixArgs& a, hipStream_t stream);
 
 }  // namespace lscan

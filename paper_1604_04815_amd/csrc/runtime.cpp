@@ -1739,7 +1739,7 @@ lscan_status lscan_radix_offsets(const void* keys, int64_t n, lscan_dtype dt, in
     // enough workgroups to fill the device, each writing a run of counts per
     // digit; the table of a workgroup stays within 32 KiB of LDS
     const int64_t want = (m + 1023) / 1024;
-    a.group = std::max<int64_t>(1, std::min<int64_t>(want, 8192 / (digits + 1)));
+    a.group = std::max<int64_t>(1, std::min<int64_t>(want, 8192 / digits));
     a.counts = offsets;
     a.key_bytes = kb;
     a.shift = shift;

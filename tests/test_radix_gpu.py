@@ -98,3 +98,13 @@ def test_radix_rounds_and_ends(gpu_lib, dtype, block, off_items):
         kbits, host = keys_for(dtype, n, seed=n)
         got = device_offsets(gpu_lib, host, dtype, 9, 8, block, offset_items=off_items)
         assert np.array_equal(got, oracle.radix_offsets(kbits, 9, 8, block)), n
+
+
+def test_radix_full_tables(gpu_lib):
+    # the largest group at every number of bits: the table takes all of its LDS
+    for bits in range(1, 9):
+        block, group = 8, 8192 >> bits
+        n = (group + 1) * 1024 * block + 3
+        kbits, host = keys_for("int32", n, seed=bits)
+        got = device_offsets(gpu_lib, host, "int32", 3, bits, block)
+        assert np.array_equal(got, oracle.radix_offsets(kbits, 3, bits, block)), bits
