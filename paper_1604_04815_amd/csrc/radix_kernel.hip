@@ -40,14 +40,14 @@ constexpr int kHistThreads = 256;
 constexpr int kHistThreadsWide = 1024;
 constexpr int kMaxDigits = 256;
 
-// Launches of at most two workgroups per CU with large blocks take 1024
+// Launches of at most two workgroups per CU (of 256) with large blocks take 1024
 // threads and four vectors in flight per thread: 256 threads leave the CUs
 // short of loads (int32 keys, 48 blocks of 2^20: 82 against 195 us; 382:
-// 253 / 356; 501 blocks of 100 000: 38 / 44).  With more workgroups the chip
-// is full either way and the 1024 threads of a block wait on its barrier
-// (763 blocks of 65 536: 41 against 37 us).
+// 253 / 356; 501 blocks of 100 000: 38 / 44; int64 keys, 367 blocks of 16 384:
+// 14.5 / 18.3).  With more workgroups the chip is full either way and the 1024
+// threads of a block wait on its barrier (763 blocks of 65 536: 41 against 37 us).
 constexpr int64_t kHistWideGroups = 512;
-constexpr int64_t kHistWideItems = 32768;
+constexpr int64_t kHistWideBytes = int64_t(128) << 10;  // of keys per block
 
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
 typedef u32x4v VecU __attribute__((aligned(4)));  // keys need no more than their own alignment
@@ -167,7 +167,7 @@ hipError_t launch_digit_counts(const RadixArgs& a, hipStream_t stream)
     const int64_t groups = (a.num_blocks + a.group - 1) / a.group;
     const size_t table_bytes = size_t(a.group) * size_t(1 << a.bits) * sizeof(uint32_t);
     (void)hipGetLastError();
-    const bool wide = groups <= kHistWideGroups && a.block_items >= kHistWideItems;
+    const bool wide = groups <= kHistWideGroups && a.block_items >= kHistWideBytes / a.key_bytes;
     auto kernel = a.key_bytes == 4 ? (wide ? digit_count_kernel<uint32_t, kHistThreadsWide>
                                            : digit_count_kernel<uint32_t, kHistThreads>)
                                    : (wide ? digit_count_kernel<uint64_t, kHistThreadsWide>

@@ -108,3 +108,9 @@ def test_radix_full_tables(gpu_lib):
         kbits, host = keys_for("int32", n, seed=bits)
         got = device_offsets(gpu_lib, host, "int32", 3, bits, block)
         assert np.array_equal(got, oracle.radix_offsets(kbits, 3, bits, block)), bits
+    # wide workgroups: 128 KiB of keys per block
+    for dtype, block in (("int64", 16_384), ("int64", 16_383), ("int32", 32_768)):
+        n = 500 * block + 77
+        kbits, host = keys_for(dtype, n, seed=8)
+        got = device_offsets(gpu_lib, host, dtype, 11, 8, block, offset_items=1)
+        assert np.array_equal(got, oracle.radix_offsets(kbits, 11, 8, block)), (dtype, block)
