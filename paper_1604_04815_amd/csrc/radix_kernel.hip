@@ -21,9 +21,9 @@
 // and of the blocks.  Measured with the scan of the counts, int32 keys, 8
 // bits, before and after: 50 million keys in blocks of 4096 54.7 / 53.3 us,
 // the same off a 16-byte line 84.7 / 51.5, 300 million 304 / 296 (4.1 TB/s
-// of keys), 50 million in blocks of 1000 with 4 bits 67 / 59.  Four vectors
-// in flight at 256 threads take 252 against 245 us where the reads already
-// run at the copy rate (400 million keys in blocks of 100 000).  The LDS of a workgroup, 8 KiB of histograms and up to 32 KiB of
+// of keys).  Four vectors in flight at 256 threads take 252 against 245 us
+// where the reads already run at the copy rate (400 million keys in blocks of
+// 100 000).  The LDS of a workgroup, 8 KiB of histograms and up to 32 KiB of
 // table, lets exactly four share a CU: 2^27 keys in blocks of 4096 are 1024
 // workgroups, all resident at once (122 us; 31 blocks in a padded table
 // instead of 32 160 us, for the 33 workgroups left over).
@@ -39,6 +39,14 @@ namespace {
 constexpr int kHistThreads = 256;
 constexpr int kHistThreadsWide = 1024;
 constexpr int kMaxDigits = 256;
+
+// Blocks of at most this many keys per thread are read key by key, the others as
+// vectors: a vector leaves most of the threads of a small block without work
+// (with the scan, 4 bits, 50 million int32 keys: blocks of 64 437 us against
+// 812 as vectors, 500 60 / 105, 1000 44 / 59; int64 keys: 500 94 / 111, 700 79 /
+// 97, but 1000 78 / 72).
+template <class K>
+constexpr int kOwnKeys = sizeof(K) == 4 ? 4 : 3;
 
 // Launches of at most two workgroups per CU (of 256) with large blocks take 1024
 // threads and four vectors in flight per thread: 256 threads leave the CUs
@@ -108,33 +116,10 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
     };
     auto block_end = [&](int64_t first) { return first + a.block_items < a.n ? first + a.block_items : a.n; };
 
-    int64_t lo = b0 * a.block_items;
-    if (last_vec >= 0) load_round(lo, block_end(lo));
-    for (int g = 0; g < gcount; ++g, lo += a.block_items) {
-        const int64_t hi = block_end(lo);
-        const int64_t v_end = hi - (hi - lo) % E;
-        uint32_t* hist = s_wave_hist[g & 1][wave];
-        for (int64_t base = lo; base < v_end; base += kVecs * kStride) {
-            u32x4v now[kVecs];
-#pragma unroll
-            for (int u = 0; u < kVecs; ++u) now[u] = w[u];
-            // the next round's vectors are in flight while this one is counted
-            const bool full = base + kVecs * kStride <= v_end;
-            const bool more = base + kVecs * kStride < v_end;
-            if (more || g + 1 < gcount) load_round(more ? base + kVecs * kStride : hi, more ? v_end : block_end(hi));
-#pragma unroll
-            for (int u = 0; u < kVecs; ++u) {
-                if (full || base + u * kStride + tid * E < v_end) {
-                    K k[E];
-                    __builtin_memcpy(k, &now[u], 16);
-#pragma unroll
-                    for (int e = 0; e < E; ++e) atomicAdd(&hist[digit_of(k[e], a.shift, mask)], 1u);
-                }
-            }
-        }
-        if (v_end + tid < hi) atomicAdd(&hist[digit_of(keys[v_end + tid], a.shift, mask)], 1u);
-        // The other histogram is clear here: its last counts were summed
-        // before this barrier by every thread.
+    // Block g's counts: the waves' histograms summed into the table and cleared.
+    // The other set of histograms is clear at the barrier: its last counts were
+    // summed before it by every thread.
+    auto sum_block = [&](int g) {
         __syncthreads();
         for (int d = tid; d < digits; d += THREADS) {
             uint32_t c = 0;
@@ -144,6 +129,71 @@ __global__ void __launch_bounds__(THREADS) digit_count_kernel(RadixArgs a)
                 s_wave_hist[g & 1][v][d] = 0;
             }
             entry(g, d) = c;
+        }
+    };
+
+    int64_t lo = b0 * a.block_items;
+    if (THREADS == kHistThreads && a.block_items <= kOwnKeys<K> * THREADS) {
+        // the next block's keys are in flight while this one's are counted
+        K key[kOwnKeys<K>], now[kOwnKeys<K>];
+        auto load_keys = [&](int64_t first) {
+#pragma unroll
+            for (int u = 0; u < kOwnKeys<K>; ++u) {
+                if (u * THREADS >= a.block_items) break;
+                const int64_t q = first + u * THREADS + tid;
+                if (q < block_end(first)) key[u] = keys[q];
+            }
+        };
+        load_keys(lo);
+        for (int g = 0; g < gcount; ++g, lo += a.block_items) {
+            const int64_t hi = block_end(lo);
+#pragma unroll
+            for (int u = 0; u < kOwnKeys<K>; ++u) now[u] = key[u];
+            if (g + 1 < gcount) load_keys(hi);
+#pragma unroll
+            for (int u = 0; u < kOwnKeys<K>; ++u) {
+                if (u * THREADS >= a.block_items) break;
+                if (lo + u * THREADS + tid < hi) atomicAdd(&s_wave_hist[g & 1][wave][digit_of(now[u], a.shift, mask)], 1u);
+            }
+            sum_block(g);
+        }
+    } else {
+        // the keys after a block's last whole vector, loaded a block ahead too (where
+        // the blocks are whole vectors, only the array's last block has any)
+        const bool tails = a.block_items % E != 0;
+        K tail = K(0);
+        auto load_tail = [&](int64_t first) {
+            const int64_t end = block_end(first), q = end - (end - first) % E + tid;
+            if (q < end) tail = keys[q];
+        };
+        if (last_vec >= 0) load_round(lo, block_end(lo));
+        if (tails) load_tail(lo);
+        for (int g = 0; g < gcount; ++g, lo += a.block_items) {
+            const int64_t hi = block_end(lo);
+            const int64_t v_end = hi - (hi - lo) % E;
+            uint32_t* hist = s_wave_hist[g & 1][wave];
+            const K last = tail;
+            if (tails && g + 1 < gcount) load_tail(hi);
+            for (int64_t base = lo; base < v_end; base += kVecs * kStride) {
+                u32x4v now[kVecs];
+#pragma unroll
+                for (int u = 0; u < kVecs; ++u) now[u] = w[u];
+                // the next round's vectors are in flight while this one is counted
+                const bool full = base + kVecs * kStride <= v_end;
+                const bool more = base + kVecs * kStride < v_end;
+                if (more || g + 1 < gcount) load_round(more ? base + kVecs * kStride : hi, more ? v_end : block_end(hi));
+#pragma unroll
+                for (int u = 0; u < kVecs; ++u) {
+                    if (full || base + u * kStride + tid * E < v_end) {
+                        K k[E];
+                        __builtin_memcpy(k, &now[u], 16);
+#pragma unroll
+                        for (int e = 0; e < E; ++e) atomicAdd(&hist[digit_of(k[e], a.shift, mask)], 1u);
+                    }
+                }
+            }
+            if (v_end + tid < hi) atomicAdd(&hist[digit_of(tails ? last : keys[v_end + tid], a.shift, mask)], 1u);
+            sum_block(g);
         }
     }
     __syncthreads();

@@ -100,6 +100,20 @@ def test_radix_rounds_and_ends(gpu_lib, dtype, block, off_items):
         assert np.array_equal(got, oracle.radix_offsets(kbits, 9, 8, block)), n
 
 
+@pytest.mark.parametrize("dtype", ["int32", "int64"])
+@pytest.mark.parametrize("bits", [1, 3, 6, 8])
+def test_radix_groups_of_blocks(gpu_lib, dtype, bits):
+    # more than 1024 blocks, so that a workgroup's table holds several: blocks read key
+    # by key (one key, a wave, up to the most a thread takes) and as vectors with and
+    # without keys after the last vector; the last block short and full
+    own = 1024 if dtype == "int32" else 768
+    for block in (1, 64, 255, 256, 257, own - 1, own, own + 1, own + 4):
+        for n in (2500 * block, 2500 * block + (block + 1) // 2):
+            kbits, host = keys_for(dtype, n, seed=n % 1000)
+            got = device_offsets(gpu_lib, host, dtype, 5, bits, block, offset_items=1)
+            assert np.array_equal(got, oracle.radix_offsets(kbits, 5, bits, block)), (block, n)
+
+
 def test_radix_full_tables(gpu_lib):
     # the largest group at every number of bits: the table takes all of its LDS
     for bits in range(1, 9):
