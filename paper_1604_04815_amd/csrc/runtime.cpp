@@ -690,13 +690,16 @@ struct Plan {
 // Where the block grid of a scan (of each array of a batch) starts: the number
 // of elements before x, fewer than a 128-byte line of outputs holds.  The grid
 // starts on a 16-byte boundary of x (full blocks read vectors); of those
-// positions, one whose outputs start on a line of y, else one whose outputs
-// start on 16 bytes (*store_vec: rows are written straight as vectors), else
-// the last before x (rows are staged).  Rows that start inside a line leave two
-// partial lines per kilobyte (int32 add 2^27, x and y 16 bytes past a line:
-// 180 us, grid on the line 169 us); reads that do cost nothing.  Where the move
-// takes another block, only arrays long enough to gain more than such a block
-// costs (5 us) move the grid to a line.
+// positions, the last whose outputs start on 16 bytes (*store_vec: rows are
+// written straight as vectors), else the last before x (rows are staged).  Rows
+// that start inside a line leave two partial lines per kilobyte; reads that do
+// cost nothing.  So long arrays move the grid further, to a position whose
+// outputs start on a line of y (int32 add, x and y 16 bytes past a line, 2^27
+// elements 180 us, on the line 169 us; 60 million 81 / 78).  A grid that starts
+// before x has a partial first block, which every other block waits for: shorter
+// arrays lose by the move (950 428 elements 7.1 / 9.0 us, 4 million in 256
+// segments 11.8 / 17.9, compensated float32 40 million 61 / 67).  Where the first
+// block is partial anyway, and the blocks stay as many, it costs nothing.
 constexpr int64_t kLineGridBytes = int64_t(256) << 20;  // of output
 int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n, bool* store_vec)
 {
@@ -707,10 +710,11 @@ int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n
     const int64_t first = int32_t(xa % 16) / k.in_bytes;
     auto out_offset = [&](int64_t ph, uint32_t unit) { return uint32_t(ya - uint64_t(ph * ob)) % unit; };
     auto blocks = [&](int64_t ph) { return n + ph <= L ? 1 : (n + ph + L - 1) / L; };
-    int64_t vec = -1;  // the first position whose outputs start on 16 bytes
+    int64_t vec = -1;  // the position whose outputs start on 16 bytes
     for (int64_t ph = first; ph < first + line; ph += step) {
         if (out_offset(ph, 16) != 0) continue;
         if (vec < 0) vec = ph;
+        if (vec == 0 && n * ob < kLineGridBytes) break;
         if (out_offset(ph, 128) == 0) {
             if (n * ob >= kLineGridBytes || blocks(ph) == blocks(vec)) vec = ph;
             break;

@@ -334,3 +334,29 @@ def test_partial_block_rows(gpu_lib, dtype, comp):
             for params in (None, gpu_lib.Params(512, 8, 1, 0)):
                 y = gpu_lib.inclusive(buf[off:], "add", compensated=comp, params=params)
                 compare(to_host(y), x, dtype, "add", False, compensated=comp, what=f"{dtype} n={n} x+{off} {params}")
+
+
+@pytest.mark.parametrize("n", [1000, 950_428, 4_000_003])
+def test_float_bits_do_not_depend_on_the_line_of_y(gpu_lib, n):
+    # x on 16 bytes and y on any 16 bytes of a line: the blocks of an output of less
+    # than 256 MiB start with the array, so float sums associate the same way
+    x = make_input("float32", "add", n + 4, seed=91)
+    base = to_device(x, "float32")
+    off = torch.arange(0, 251, device="cuda", dtype=torch.int64) * n // 250
+    buf = torch.empty(n + 64, dtype=torch.float32, device="cuda")
+    for xo in (0, 4):
+        xd = base[xo:xo + n]
+        for comp in (False, True):
+            runs = {"plain": lambda y: gpu_lib.inclusive(xd, "add", compensated=comp, out=y),
+                    "segmented": lambda y: gpu_lib.segmented(xd, off, "add", compensated=comp, out=y),
+                    "batched": lambda y: gpu_lib.batched([xd], "add", compensated=comp, outs=[y])}
+            for name, call in runs.items():
+                want = None
+                for yo in (0, 4, 16, 28):
+                    y = buf[yo:yo + n]
+                    y.fill_(7)
+                    call(y)
+                    gpu_lib.lscan_check(torch.cuda.current_stream().cuda_stream)
+                    got = y.cpu().numpy().view(np.uint32)
+                    want = got if want is None else want
+                    assert np.array_equal(got, want), (name, comp, xo, yo)
