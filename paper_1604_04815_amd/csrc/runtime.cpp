@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -725,15 +726,18 @@ int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n
 }
 
 // The path of one array of a batch: its grid phase when x is read with vectors
-// (-1: the element path).  *stage_y is set when y sits at another phase than
-// the grid, so that rows read as vectors are written through the LDS stage;
-// that needs 16-byte output vectors, else the array takes the element path.
-int64_t batch_phase(const KernelEntry& k, const lscan_array& arr, bool* stage_y)
+// (-1: the element path).  stage_y is 1 when y sits at another phase than the
+// grid, so that rows read as vectors are written through the LDS stage; that
+// needs 16-byte output vectors, else the array takes the element path.
+struct BatchPath {
+    int32_t phase, stage_y;
+};
+BatchPath batch_path(const KernelEntry& k, const lscan_array& arr)
 {
     bool store_vec = false;
     const int64_t ph = grid_phase(k, arr.x, arr.y, arr.n, &store_vec);
-    *stage_y = !store_vec && k.out_bytes * k.elems_per_vec == 16;
-    return (store_vec || *stage_y) ? ph : -1;
+    const bool stage_y = !store_vec && k.out_bytes * k.elems_per_vec == 16;
+    return BatchPath{(store_vec || stage_y) ? int32_t(ph) : -1, stage_y ? 1 : 0};
 }
 
 // Blocks of one array of a batch: its n elements after its grid phase.
@@ -814,10 +818,14 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
 
     const int64_t L = k.tile_elems;
     int64_t M = 0;
+    std::unique_ptr<BatchPath[]> paths;  // of a batch's arrays, whose blocks size the workspace that holds their table
     if (r.mode == kModeBatched) {
-        bool stage_y = false;
-        for (int64_t i = 0; i < r.num_arrays; ++i)
-            M += batch_blocks(r.arrays[i].n, batch_phase(k, r.arrays[i], &stage_y), L);
+        paths.reset(new (std::nothrow) BatchPath[size_t(r.num_arrays)]);
+        if (!paths) return LSCAN_ERR_NO_MEMORY;
+        for (int64_t i = 0; i < r.num_arrays; ++i) {
+            paths[i] = batch_path(k, r.arrays[i]);
+            M += batch_blocks(r.arrays[i].n, paths[i].phase, L);
+        }
     } else {
         M = (r.n + phase + L - 1) / L;
     }
@@ -861,10 +869,9 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
             ws->desc_host[i].y = r.arrays[i].y;
             ws->desc_host[i].n = r.arrays[i].n;
             ws->desc_host[i].first_block = first;
-            bool stage_y = false;
-            ws->desc_host[i].phase = batch_phase(k, r.arrays[i], &stage_y);
-            ws->desc_host[i].stage_y = stage_y ? 1 : 0;
-            first += batch_blocks(r.arrays[i].n, ws->desc_host[i].phase, L);
+            ws->desc_host[i].phase = paths[i].phase;
+            ws->desc_host[i].stage_y = paths[i].stage_y;
+            first += batch_blocks(r.arrays[i].n, paths[i].phase, L);
         }
         ws->desc_host[r.num_arrays] = BatchArray{nullptr, nullptr, 0, first, 0, 0};
         e = hipMemcpyAsync(ws->desc, ws->desc_host, desc_entries * sizeof(BatchArray), hipMemcpyHostToDevice,
