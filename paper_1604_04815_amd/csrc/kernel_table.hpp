@@ -99,6 +99,18 @@ enum OpCode : int {
     kNumOpCodes
 };
 
+// Whether the block grid of a plain or segmented scan with these vectors and this
+// tile may start on an odd 8 bytes: full blocks are then read straight into
+// registers, 8 bytes a lane, instead of through LDS.  The tiles that short arrays
+// take only: in 512 x 8 the choice costs long aligned arrays up to 3 % (compensated
+// bf16 2^27 156 against 160 us, segmented bf16 sum 157 against 162), and in 1024 x 4
+// where its kernels spill (compensated, 9 million 21.8 / 22.4).  block_words: of a
+// block's aggregate, 2 for compensated sums and 2 and more for segmented scans.
+constexpr bool odd_vector_grids(int vec_bytes, int threads, int vectors, int block_words)
+{
+    return vec_bytes == 8 && (threads * vectors <= 2048 || (threads == 1024 && vectors == 4 && block_words == 1));
+}
+
 // Compiled tile shapes (T, vectors per lane).
 constexpr int kNumShapes = 10;
 constexpr int kArgShortOffset = 6;  // kI32ArgMaxS - kI32ArgMax

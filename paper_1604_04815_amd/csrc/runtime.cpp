@@ -186,6 +186,17 @@ int small_compact_shape(int64_t bytes)
     return bytes <= (int64_t(8) << 20) ? 5 : -1;  // 1024 x 2
 }
 
+// Segmented bf16 scans of arrays on an odd 8 bytes: 512 x 8 starts them with a
+// partial block (see odd_vector_grids; 500 segments, add of 2.5 million 18.1 us
+// against 12.1 at 256 x 8, 4 million 18.7 / 13.5, 6 million 23.9 / 20.0; maxima of 6
+// million 21.2 / 19.6, compensated 27.7 / 26.6; at 8 million 24.0 / 23.4, maxima
+// 21.1 / 23.0).
+int small_odd_segmented_shape(int64_t bytes)
+{
+    const int s = small_segmented_shape(bytes);
+    return s < 0 && bytes <= (int64_t(12) << 20) ? 0 : s;  // 256 x 8
+}
+
 // Segmented launches of at most this many blocks per workgroup search the
 // offsets for each block instead of reading the table of first segments.
 constexpr int64_t kSearchedBlocks = 2;
@@ -702,14 +713,26 @@ struct Plan {
 // segments 11.8 / 17.9, compensated float32 40 million 61 / 67).  Where the first
 // block is partial anyway, and the blocks stay as many, it costs nothing.
 constexpr int64_t kLineGridBytes = int64_t(256) << 20;  // of output
-int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n, bool* store_vec)
+// Kernels of 8-byte vectors (bf16) need no grid on 16 bytes where they do not load
+// through LDS: always in batches, and in short arrays elsewhere, so that an array
+// on an odd 8 bytes starts its first block, too (bf16 add of 1.5 million 9.4 us with
+// a partial first block, 8.1 so, 4 million 10.2 / 8.1, 8 million 13.1 / 11.5; 9
+// million 16.3 / 16.9).  (Not user operators, whose kernels may have been built
+// before they took such grids.)
+constexpr int64_t kOddGridBytes = int64_t(16) << 20;  // of input
+enum class OddGrid { kNever, kShort, kAlways };
+int64_t grid_phase(const KernelEntry& k, const void* x, const void* y, int64_t n, OddGrid odd_grid, bool* store_vec)
 {
     const uintptr_t xa = reinterpret_cast<uintptr_t>(x), ya = reinterpret_cast<uintptr_t>(y);
     const int64_t ob = k.out_bytes, L = k.tile_elems;
     // (batches do this for every array: 32-bit divisions, none for arrays of one block)
-    const int64_t step = std::max<int32_t>(16 / k.in_bytes, 1), line = std::max<int32_t>(128 / k.out_bytes, 1);
-    const int64_t first = int32_t(xa % 16) / k.in_bytes;
-    auto out_offset = [&](int64_t ph, uint32_t unit) { return uint32_t(ya - uint64_t(ph * ob)) % unit; };
+    bool odd = odd_grid != OddGrid::kNever && xa % 16 == 8 && k.in_bytes * k.elems_per_vec == 8;
+    if (odd && odd_grid == OddGrid::kShort)
+        odd = odd_vector_grids(8, k.block_threads, k.vectors_per_lane, k.slot_words) && n * k.in_bytes <= kOddGridBytes;
+    const int32_t unit = odd ? 8 : 16;
+    const int64_t step = std::max<int32_t>(unit / k.in_bytes, 1), line = std::max<int32_t>(128 / k.out_bytes, 1);
+    const int64_t first = int32_t(xa % unit) / k.in_bytes;
+    auto out_offset = [&](int64_t ph, uint32_t to) { return uint32_t(ya - uint64_t(ph * ob)) % to; };
     auto blocks = [&](int64_t ph) { return n + ph <= L ? 1 : (n + ph + L - 1) / L; };
     int64_t vec = -1;  // the position whose outputs start on 16 bytes
     for (int64_t ph = first; ph < first + line; ph += step) {
@@ -735,7 +758,7 @@ struct BatchPath {
 BatchPath batch_path(const KernelEntry& k, const lscan_array& arr)
 {
     bool store_vec = false;
-    const int64_t ph = grid_phase(k, arr.x, arr.y, arr.n, &store_vec);
+    const int64_t ph = grid_phase(k, arr.x, arr.y, arr.n, OddGrid::kAlways, &store_vec);
     const bool stage_y = !store_vec && k.out_bytes * k.elems_per_vec == 16;
     return BatchPath{(store_vec || stage_y) ? int32_t(ph) : -1, stage_y ? 1 : 0};
 }
@@ -766,8 +789,10 @@ Params choose_params_locked(const Request& r)
     const bool small_kind = (r.mode == kModePlain && (r.oc < kI32ArgMax || r.oc >= kI32ArgMaxS)) ||
                             r.mode == kModeSegmented || r.mode == kModeCompact;
     if (!r.custom && small_kind && library_default) {
-        const int64_t bytes = r.n * int64_t(table()[r.mode][r.oc][prm.shape].in_bytes);
-        const int s = r.mode == kModeSegmented ? small_segmented_shape(bytes)
+        const KernelEntry& k = table()[r.mode][r.oc][prm.shape];
+        const int64_t bytes = r.n * int64_t(k.in_bytes);
+        const bool odd = k.in_bytes * k.elems_per_vec == 8 && reinterpret_cast<uintptr_t>(r.x) % 16 == 8;
+        const int s = r.mode == kModeSegmented ? (odd ? small_odd_segmented_shape(bytes) : small_segmented_shape(bytes))
                       : r.mode == kModeCompact ? small_compact_shape(bytes)
                       : r.oc >= kI32ArgMaxS    ? small_arg_shape(bytes)
                                                : small_array_shape(bytes);
@@ -812,7 +837,7 @@ lscan_status plan_locked(const Request& r, int dev, Workspace* ws_fixed, hipStre
     bool vec_ok = false, store_vec = false;
     if ((r.mode == kModePlain || r.mode == kModeSegmented) &&
         reinterpret_cast<uintptr_t>(r.x) % uintptr_t(k.in_bytes) == 0) {
-        phase = int32_t(grid_phase(k, r.x, r.y, r.n, &store_vec));
+        phase = int32_t(grid_phase(k, r.x, r.y, r.n, r.custom ? OddGrid::kNever : OddGrid::kShort, &store_vec));
         vec_ok = true;
     }
 

@@ -587,6 +587,10 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     // the prefetch: this wave's LDS rows, and whether they hold the block to scan next
     const uint32_t pf_lds = kPrefetch ? lds_address(&s_pf[0]) + uint32_t(wave) * kPfOps * 1024u : 0u;
     bool pf_have = false;
+    // the 16-byte LDS loads need 16-byte aligned chunks: where the grid starts on an
+    // odd 8 bytes (odd_vector_grids), full blocks are loaded straight into registers
+    const bool pf_ok = kPrefetch && (!odd_vector_grids(kVecBytes, T, R, W) ||
+                                     ((reinterpret_cast<uintptr_t>(a.x) - uintptr_t(a.phase) * sizeof(In)) & 15u) == 0);
     // the previous step wrote its pending block with at least R vector stores per
     // wave, all issued after the prefetch that the next step waits for
     bool pf_then_stores = false;
@@ -662,7 +666,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
         } else {
             xg = static_cast<const In*>(a.x) - a.phase;
             t0 = i * L;
-            return a.vec_ok != 0 && t0 + L <= a.n + a.phase && t0 >= a.phase;
+            return pf_ok && a.vec_ok != 0 && t0 + L <= a.n + a.phase && t0 >= a.phase;
         }
     };
     if constexpr (kPrefetch) {
@@ -738,7 +742,7 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
             lane0 = tile0 + int64_t(wave) * (R * ROW) + int64_t(lane) * kLaneElems;
             full = vec_ok && (tile0 + L <= n) && (tile0 >= ph);
             if (full) {
-                if constexpr (kPrefetch) {
+                if (kPrefetch && pf_ok) {
                     // a full block arrives through LDS: prefetched during the previous
                     // step (or, after a partial block, loaded that way now), so no
                     // data load of the compiler's own is ever pending past this point
@@ -774,6 +778,10 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
                 } else {
 #pragma unroll
                     for (int r = 0; r < R; ++r) load_vector<In, E>(x + lane0 + int64_t(r) * kRowStep, raw[r]);
+                    if constexpr (kPrefetch) {  // off the path of the LDS reads
+#pragma unroll
+                        for (int r = 0; r < R; ++r) complete_loads(raw[r]);
+                    }
                 }
             } else {
                 // an array's first or last block, or one that cannot use vectors: whole

@@ -360,3 +360,27 @@ def test_float_bits_do_not_depend_on_the_line_of_y(gpu_lib, n):
                     got = y.cpu().numpy().view(np.uint32)
                     want = got if want is None else want
                     assert np.array_equal(got, want), (name, comp, xo, yo)
+
+
+@pytest.mark.parametrize("n", [1000, 4097, 70_001, (6 << 20) + 3, 8 << 20, (8 << 20) + 1])
+def test_bf16_on_an_odd_eight_bytes(gpu_lib, n):
+    # short arrays start their blocks on the array's 8 bytes and read them without LDS,
+    # longer ones start them 4 elements earlier: around the lengths where that changes
+    # (plain, segmented, and a batch, which always starts with its arrays)
+    for op, comp in (("add", False), ("max", False), ("add", True)):
+        x = make_input("bfloat16", op, n + 16, seed=17)
+        off = np.unique(np.concatenate([[0, n], np.random.default_rng(n).integers(0, n, 40)])).astype(np.int64)
+        base = to_device(x, "bfloat16")
+        buf = torch.empty(n + 16, dtype=torch.float32, device="cuda")
+        od = torch.from_numpy(off).to("cuda")
+        for xo, yo in ((4, 0), (12, 4), (4, 1)):
+            xd, xh, y = base[xo:xo + n], x[xo:xo + n], buf[yo:yo + n]
+            for name, call, kw in (
+                    ("plain", lambda: gpu_lib.inclusive(xd, op, compensated=comp, out=y), {}),
+                    ("segmented", lambda: gpu_lib.segmented(xd, od, op, compensated=comp, out=y), {"offsets": off}),
+                    ("batched", lambda: gpu_lib.batched([xd], op, compensated=comp, outs=[y]), {})):
+                buf.fill_(7)
+                call()
+                gpu_lib.lscan_check(torch.cuda.current_stream().cuda_stream)
+                compare(to_host(y), xh, "bfloat16", op, False, comp, what=f"{name} {op} n={n} x+{xo} y+{yo}", **kw)
+                assert torch.all(buf[:yo] == 7).item() and torch.all(buf[yo + n:] == 7).item()
