@@ -24,13 +24,12 @@
  *
  * Pointers: x, y and offsets are DEVICE pointers owned by the caller, who
  * keeps them valid until the work completes (stream order).  x and y must be
- * aligned to their element size.  Full blocks use 16-byte vectors when x
- * sits on a vector boundary (16 bytes; 8 for bf16) and y on 16 bytes, or
- * when x and y sit the same number of elements past such boundaries (the
- * block grid is then shifted by that many elements).  Plain and segmented
- * scans whose y sits at another phase than x still read vectors and write
- * aligned vectors staged through LDS; batched arrays in that case move
- * every element on its own (slower).
+ * aligned to their element size.  Full blocks read whole vectors whatever
+ * the alignment: the blocks then start a few elements before the array, the
+ * first of them with nothing in those places.  They write whole vectors
+ * too, straight when y sits at the same place past a 16-byte boundary as
+ * that start, through an LDS stage otherwise (outputs wider than their
+ * inputs: argmax / argmin, element by element).
  * y == x (in place) is allowed when input and output types are equal
  * (Section 4.5 of the paper: every element is read once before it is written
  * once); any other overlap is rejected.  Streams are hipStream_t passed as
@@ -108,7 +107,10 @@ typedef enum {
 #define LSCAN_F_COMPENSATED 0x1u /* F32/BF16 add: carry a TwoSum error term */
 /* LSCAN_F_DETERMINISTIC asks for a fixed association of the float sums; it
  * is accepted everywhere and always met: both hand-offs fold in a fixed
- * order, so one tile shape and grid give the same bits on every run. */
+ * order, so one tile shape and grid give the same bits on every run.  Where
+ * the blocks start depends on where x lies within 16 bytes and, if that is
+ * not on 16 bytes or the output has at least 256 MiB, on where y lies within
+ * 128 bytes: arrays at other such places may associate otherwise. */
 #define LSCAN_F_DETERMINISTIC 0x2u
 #define LSCAN_F_EXCLUSIVE 0x4u   /* lscan_segmented only: exclusive scan */
 /* LSCAN_F_INDEX64: running argmax / argmin only -- run the kernels that
@@ -138,7 +140,8 @@ typedef int32_t lscan_status;
  *   flags  0 or LSCAN_F_COMPENSATED (F32/BF16 with LSCAN_ADD only, else
  *          LSCAN_ERR_UNSUPPORTED), optionally | LSCAN_F_DETERMINISTIC
  * Float add results depend on the association fixed by the launch
- * parameters; for a fixed parameter set they are deterministic.
+ * parameters and by the alignment of x and y (LSCAN_F_DETERMINISTIC); for a
+ * fixed parameter set and alignment they are deterministic.
  */
 lscan_status lscan_inclusive(const void *x, void *y, int64_t n, lscan_dtype dt,
                              lscan_op op, uint32_t flags, void *stream);
@@ -425,13 +428,14 @@ lscan_status lscan_scan_custom(const lscan_custom_kernel *kernel,
  *                outside [0, num_vertices) in such a row; those are
  *                skipped, never dereferenced)
  * Outputs may not overlap the inputs or each other.  The library keeps a
- * per-stream workspace of about 40 bytes per vertex and 24 bytes per 1024
+ * per-stream workspace of about 41 bytes per vertex and 24 bytes per 2048
  * edges.  Not capturable into a HIP graph (LSCAN_ERR_UNSUPPORTED while the
  * stream captures: each launch takes fresh flag tags from the host).  A wait
  * that outlasts the watchdog stops the whole grid; the next lscan_check on
  * the stream reports LSCAN_ERR_TIMEOUT and the outputs are undefined.
- * lscan_bfs_with_params honours groups_per_cu only (a tile shape or the
- * chain hand-off: LSCAN_ERR_UNSUPPORTED).
+ * lscan_bfs_with_params takes groups_per_cu only (a tile shape or the
+ * chain hand-off: LSCAN_ERR_UNSUPPORTED), as an upper limit: a workgroup of
+ * the search holds most of a CU's LDS, so one per CU runs whatever the limit.
  */
 lscan_status lscan_bfs(const int64_t *row_offsets, const int32_t *cols,
                        int64_t num_vertices, int64_t num_edges, int32_t source,
@@ -569,7 +573,9 @@ lscan_status lscan_server_destroy(lscan_server *s);
  * counts, search offsets and level barriers): a wait that lasts longer than
  * `us` microseconds of the device's constant clock gives up, the grid stops
  * (each waiter sees the abort word) and the next lscan_check on the stream
- * reports LSCAN_ERR_TIMEOUT; the outputs of that launch are undefined.
+ * reports LSCAN_ERR_TIMEOUT; the outputs of that launch are undefined.  (A
+ * level barrier of the search may last through 32 levels of at most 2048
+ * edges, which one workgroup runs while the others wait.)
  * Applies to launches made after the call, on every device (a captured
  * graph keeps the value it was captured with).  Default 2,000,000 (2 s).
  * 0 gives up at the first wait not already satisfied -- a way to exercise

@@ -1020,7 +1020,9 @@ lscan_status order_after_locked(DeviceOrder* order, hipStream_t stream)
 // ever handed to HIP (kernel arguments, memsets, copies).
 constexpr size_t kNoAllocCtrlWords = 32;               // 256 bytes; the kernels use 7 32-bit words
 constexpr size_t kNoAllocSlotWords = size_t(1) << 19;  // 4 MiB of 64-bit flag words
-constexpr size_t kNoAllocSpareWords = 8;  // one more block: a grid shifted by more than one vector
+// Beyond those 4 MiB: one more block's words, for a grid that starts more than the
+// one vector before the array that noalloc_fits_locked counts.
+constexpr size_t kNoAllocSpareWords = 8;
 static __device__ __align__(256) uint64_t scratch[kNoAllocCtrlWords + kNoAllocSlotWords + kNoAllocSpareWords];
 
 constexpr int kMaxNoAllocDevices = 64;
@@ -1055,8 +1057,9 @@ lscan_status noalloc_workspace_locked(int dev, hipStream_t stream, Workspace** o
 
 // Whether the flag words of request r fit the fixed workspace, decided from
 // host data before any device work: M blocks of the kernel r would run
-// (counting a shift of the block grid by one vector) times its flag words per
-// block.  Called with g_mu held.
+// (counting a shift of the block grid by one vector; a shift by more takes at
+// most one block more, whose words are kNoAllocSpareWords) times its flag words
+// per block.  Called with g_mu held.
 bool noalloc_fits_locked(const Request& r)
 {
     const Params prm = choose_params_locked(r);

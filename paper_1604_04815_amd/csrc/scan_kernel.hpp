@@ -682,8 +682,9 @@ __global__ void __launch_bounds__(T, (kMinWavesPerSimd<BaseOp, T, R, MODE>)) sca
     // latency bound (4096 segments, int32 add 2^27: 197 -> 192 us; compensated
     // float32 178 -> 174, int64 max 192 -> 177, bf16 segmented max 223 -> 198).  Long
     // plain scans at the rate of a copy keep the choice per row: without it they
-    // lose 2.5 % (int32 add 2^28: 334 -> 342 us, however its stores are spaced).
-    // (Short ones gain 3 % by it: 2^20 6.9 -> 6.7 us.)
+    // lose 2 % (int32 add 2^28: 334 -> 342 us, however its stores are spaced; int64
+    // add 2^27: 322 -> 328).  (Short ones gain 3 % by it: 2^20 6.9 -> 6.7 us; not
+    // int64 add, 10^6 7.0 -> 7.7.)
     constexpr bool kStraight = MODE != kModePlain || kBlocked || kStage32 ||
                                (sizeof(V) > 4 && !std::is_same<BaseOp, AddI64>::value);
     constexpr bool kStraightIfShort = sizeof(V) == 4;

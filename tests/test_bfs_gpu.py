@@ -373,3 +373,13 @@ def test_many_chunks_per_workgroup(gpu_lib, with_parents):
     for _ in range(3):
         levels, parents, stats = run(gpu_lib, row, col, 0, with_parents=with_parents)
         check(row, col, 0, levels, parents, stats, "many chunks")
+
+
+@pytest.mark.parametrize("groups", [1, 2, 8])
+def test_one_workgroup_per_cu(gpu_lib, groups):
+    # the limit is accepted and one workgroup per CU runs: a second does not fit the LDS
+    row, col = csr(np.arange(99), np.arange(1, 100), 100)
+    levels, parents, stats = run(gpu_lib, row, col, 0, params=gpu_lib.Params(0, 0, groups, 0))
+    check(row, col, 0, levels, parents, stats, f"limit {groups}")
+    info = gpu_lib.lscan_last_launch()
+    assert info.groups_per_cu == 1 and info.occupancy == 1
