@@ -109,8 +109,9 @@ typedef enum {
  * is accepted everywhere and always met: both hand-offs fold in a fixed
  * order, so one tile shape and grid give the same bits on every run.  Where
  * the blocks start depends on where x lies within 16 bytes and, if that is
- * not on 16 bytes or the output has at least 256 MiB, on where y lies within
- * 128 bytes: arrays at other such places may associate otherwise. */
+ * not on 16 bytes, the output has at least 256 MiB or the array is one of a
+ * batch, on where y lies within 128 bytes: arrays at other such places may
+ * associate otherwise. */
 #define LSCAN_F_DETERMINISTIC 0x2u
 #define LSCAN_F_EXCLUSIVE 0x4u   /* lscan_segmented only: exclusive scan */
 /* LSCAN_F_INDEX64: running argmax / argmin only -- run the kernels that

@@ -348,8 +348,7 @@ def test_float_bits_do_not_depend_on_the_line_of_y(gpu_lib, n):
         xd = base[xo:xo + n]
         for comp in (False, True):
             runs = {"plain": lambda y: gpu_lib.inclusive(xd, "add", compensated=comp, out=y),
-                    "segmented": lambda y: gpu_lib.segmented(xd, off, "add", compensated=comp, out=y),
-                    "batched": lambda y: gpu_lib.batched([xd], "add", compensated=comp, outs=[y])}
+                    "segmented": lambda y: gpu_lib.segmented(xd, off, "add", compensated=comp, out=y)}
             for name, call in runs.items():
                 want = None
                 for yo in (0, 4, 16, 28):
