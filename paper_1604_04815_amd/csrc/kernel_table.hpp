@@ -16,7 +16,7 @@ struct BatchArray {
     int64_t n;
     int64_t first_block;
     int64_t phase;    // -1: element path; else the array's blocks start this many positions before
-                      // it (a 16-byte boundary of x) and cover n + phase positions
+                      // it (where vectors of x start) and cover n + phase positions
     int64_t stage_y;  // 1: y sits at another phase than x; rows read as vectors are
                       // written through the LDS stage as aligned vectors
 };
@@ -45,7 +45,7 @@ struct ScanArgs {
     int32_t exclusive;        // 1: exclusive scan
     int32_t vec_ok;           // 1: full blocks read x with full-width vectors
     int32_t phase;            // plain and segmented scans: the block grid starts this many elements
-                              // before x, on a 16-byte boundary of x
+                              // before x, where vectors of x start (odd_vector_grids)
     int32_t store_vec;        // plain and segmented scans: 1 when y sits at the same phase, so full
                               // blocks also write vectors directly (else through an LDS stage, or
                               // element by element for 32-byte output vectors)

@@ -701,7 +701,7 @@ struct Plan {
 
 // Where the block grid of a scan (of each array of a batch) starts: the number
 // of elements before x, fewer than a 128-byte line of outputs holds.  The grid
-// starts on a 16-byte boundary of x (full blocks read vectors); of those
+// starts on a 16-byte boundary of x (full blocks read vectors; odd: 8); of those
 // positions, the last whose outputs start on 16 bytes (*store_vec: rows are
 // written straight as vectors), else the last before x (rows are staged).  Rows
 // that start inside a line leave two partial lines per kilobyte; reads that do
@@ -718,7 +718,7 @@ constexpr int64_t kLineGridBytes = int64_t(256) << 20;  // of output
 // Kernels of 8-byte vectors (bf16) need no grid on 16 bytes where they do not load
 // through LDS: always in batches, and in short arrays elsewhere, so that an array
 // on an odd 8 bytes starts its first block, too (bf16 add of 1.5 million 9.4 us with
-// a partial first block, 8.1 so, 4 million 10.2 / 8.1, 8 million 13.1 / 11.5; 9
+// a partial first block, 8.1 so, 4 million 10.2 / 8.4, 8 million 13.1 / 11.9; 9
 // million 16.3 / 16.9).  (Not user operators, whose kernels may have been built
 // before they took such grids.)
 constexpr int64_t kOddGridBytes = int64_t(16) << 20;  // of input
